@@ -269,14 +269,12 @@ __device__ __forceinline__ T chi2_of(const Trk<T>& k, T my, T mz, const SInv<T>&
   return r0 * r0 * si.i00 + (T)2 * r0 * r1 * si.i01 + r1 * r1 * si.i11;
 }
 
-// Kalman update with a (y, z) measurement.  Returns false (state untouched)
-// if |sin phi| >= 1 afterwards.
+// Kalman update with a (y, z) measurement, si the inverse residual
+// covariance.  Returns false (state untouched) if |sin phi| >= 1 afterwards.
 template <typename T>
-__device__ __forceinline__ bool update(Trk<T>& k, T my, T mz, T vy, T vz, T* chi2) {
+__device__ __forceinline__ bool update(Trk<T>& k, T my, T mz, const SInv<T>& si) {
   const T r0 = my - k.p[0], r1 = mz - k.p[1];
-  const SInv<T> si = s_inverse(k, vy, vz);
   const T I00 = si.i00, I01 = si.i01, I11 = si.i11;
-  if (chi2) *chi2 = r0 * r0 * I00 + (T)2 * r0 * r1 * I01 + r1 * r1 * I11;
   T K0[5], K1[5], c0[5], c1v[5];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
@@ -337,15 +335,35 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base) {
                                            0x00020000);
 }
 
+// The better of two lanes' candidates (least chi2, the lower index on ties;
+// -1 if neither has one), the other lane being the one that the DPP control
+// CTRL names (a permutation of the lanes of each four).
+template <int CTRL>
+__device__ __forceinline__ void better_of(int32_t& best, float& bchi, int2& bq) {
+  const int32_t ob = __builtin_amdgcn_mov_dpp(best, CTRL, 0xF, 0xF, false);
+  const float oc = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(bchi), CTRL, 0xF, 0xF, false));
+  const int32_t ox = __builtin_amdgcn_mov_dpp(bq.x, CTRL, 0xF, 0xF, false);
+  const int32_t oy = __builtin_amdgcn_mov_dpp(bq.y, CTRL, 0xF, 0xF, false);
+  const bool take = ob >= 0 && (best < 0 || oc < bchi || (oc == bchi && ob < best));
+  best = take ? ob : best;
+  bchi = take ? oc : bchi;
+  bq.x = take ? ox : bq.x;
+  bq.y = take ? oy : bq.y;
+}
+
 // Best candidate of row ur for the track state k: the cluster with the least
 // chi2 within the cut, the lower index on ties (-1 if none).  Only the grid
 // blocks within the z residual bound that chi2 alone sets (plus a margin) are
-// scanned; bq receives the chosen cluster's position.
+// scanned; bq receives the chosen cluster's position.  With a group of G > 1
+// lanes (all holding k, and all calling), each lane takes every G-th pair of
+// candidates and the group's best is agreed on at the end: the same cluster.
 __device__ __forceinline__ int32_t search_row(const ClusterView& cl, const uint32_t* cblk,
                                               uint32_t nblk, uint32_t ur, const Trk<float>& k,
-                                              int32_t anchor, float vy, float vz, float chi2max,
-                                              uint32_t& n_cand, int2& bq) {
-  const float w = sqrtf(chi2max * (k.c[5] + vz));
+                                              int32_t anchor, float vz, const SInv<float>& si,
+                                              float chi2max, uint32_t& n_cand, int2& bq,
+                                              uint32_t G = 1, uint32_t sub = 0) {
+  // the hardware square root (1 ulp): the margin of 3 bins below covers it
+  const float w = __builtin_amdgcn_sqrtf(chi2max * (k.c[5] + vz));
   const float zabs = k.p[1] + (float)anchor * (float)FX_SCALE;
   const float flo = floorf(2.0f * (zabs - w)) - 3.0f, fhi = ceilf(2.0f * (zabs + w)) + 3.0f;
   // NaN or out-of-range windows collapse to an empty or clamped block range
@@ -383,10 +401,9 @@ __device__ __forceinline__ int32_t search_row(const ClusterView& cl, const uint3
   if (b > s1) b = s1;
   int32_t best = -1;
   float bchi = 0.0f;
-  const SInv<float> si = s_inverse(k, vy, vz);
   n_cand += b - a;
   // candidates in index order, two at a time (both loads of a pair in flight)
-  for (uint32_t c0 = a; c0 < b; c0 += 2) {
+  for (uint32_t c0 = a + 2 * sub; c0 < b; c0 += 2 * G) {
     int2 q[2];
     if (c0 + 1 < b) {
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(buffer_of(cl.pos), (int)(c0 * 8u), 0, 0);
@@ -409,6 +426,9 @@ __device__ __forceinline__ int32_t search_row(const ClusterView& cl, const uint3
       }
     }
   }
+  // the least chi2 of the group, the lower index on ties
+  if (G >= 2) better_of<0xB1>(best, bchi, bq);  // lanes 1 0 3 2 of each four
+  if (G >= 4) better_of<0x4E>(best, bchi, bq);  // lanes 2 3 0 1
   return best;
 }
 
@@ -575,6 +595,8 @@ struct FollowLane {
   int32_t pre;    // candidate of the next row known before its helix step, or -1
   uint32_t ubase;
   int r, r1, L, nmiss, nh, hi, lo, rs;  // rs: row of sp
+  int pend_row;       // row whose hit-table entry is still to be stored, or -1
+  int32_t pend_hit;
   uint32_t n_steps, n_cands, n_upds;      // work done (measurement)
 };
 
@@ -582,10 +604,13 @@ struct FollowLane {
 __device__ __forceinline__ bool follow_init(FollowLane& f, uint32_t t, const ClusterView& cl,
                                             const uint32_t* tl_start, const uint16_t* tl_len,
                                             const int32_t* upc, const uint32_t* pts, FollowOut& fo,
-                                            const DevParams32* P, const PV<float>& pv) {
-  fo.ok[t] = 0;
-  fo.nhits[t] = 0;
-  fo.range[t] = 0;
+                                            const DevParams32* P, const PV<float>& pv,
+                                            bool lead = true) {
+  if (lead) {
+    fo.ok[t] = 0;
+    fo.nhits[t] = 0;
+    fo.range[t] = 0;
+  }
   const uint32_t M = pts[(size_t)t * 3 + 0], E = pts[(size_t)t * 3 + 1];
   if (M == 0xFFFFFFFFu) return false;
   const uint32_t urA = pts[(size_t)t * 3 + 2];
@@ -627,8 +652,8 @@ __device__ __forceinline__ bool follow_init(FollowLane& f, uint32_t t, const Clu
   if (!(fabsf(k.p[2]) < pv.snp_max())) return false;
   c0_reset(k, pv, r1);
   f.n_upds += 1;
-  if (!update(k, k.p[0], 0.0f, pv.vy(r1), pv.vz(r1), (float*)nullptr)) return false;
-  fo.hits[(size_t)t * NROW + r1] = (int32_t)A;
+  if (!update(k, k.p[0], 0.0f, s_inverse(k, pv.vy(r1), pv.vz(r1)))) return false;
+  if (lead) fo.hits[(size_t)t * NROW + r1] = (int32_t)A;
   f.nh = 1;
 #pragma unroll
   for (int i = 0; i < 5; ++i) f.sp[i] = k.p[i];
@@ -637,7 +662,17 @@ __device__ __forceinline__ bool follow_init(FollowLane& f, uint32_t t, const Clu
   f.hi = r1;
   f.pre = L > 1 ? upc[A] : -1;  // the next row is on the tracklet's own chain
   f.r = r1;
+  f.pend_row = -1;
   return true;
+}
+
+// The pending hit-table store of a tracklet.  A row's entry is stored while
+// the next row's helix step runs (or at the end of the pass): the waits on the
+// loads that follow a store also wait for the store to complete, and issued at
+// the end of its own step it would hold up the next one.
+__device__ __forceinline__ void follow_flush(FollowLane& f, const FollowOut& fo, bool lead) {
+  if (f.pend_row >= 0 && lead) fo.hits[(size_t)f.t * NROW + f.pend_row] = f.pend_hit;
+  f.pend_row = -1;
 }
 
 // Pass B start: the outermost pass-A hit (row rs) with a reset covariance;
@@ -654,12 +689,13 @@ __device__ __forceinline__ bool follow_start_b(FollowLane& f, const ClusterView&
   const float my = (float)q.x * (float)FX_SCALE;
   const float mz = (float)(q.y - f.anchor) * (float)FX_SCALE;
   ++f.n_upds;
-  if (!update(k, my, mz, pv.vy(f.rs), pv.vz(f.rs), (float*)nullptr)) return false;
+  if (!update(k, my, mz, s_inverse(k, pv.vy(f.rs), pv.vz(f.rs)))) return false;
 #pragma unroll
   for (int i = 0; i < 5; ++i) f.sp[i] = k.p[i];
   f.nmiss = 0;
   f.r = f.rs;
   f.pre = f.rs - 1 >= f.r1 ? fo.hits[(size_t)f.t * NROW + f.rs - 1] : -1;
+  f.pend_row = -1;
   return true;
 }
 
@@ -675,13 +711,16 @@ __device__ __forceinline__ void follow_finish(const FollowLane& f, FollowOut& fo
 }
 
 // One row of pass A (outward, PA = 1) or pass B (inward, PA = 0).  Returns
-// true when the pass has ended.
+// true when the pass has ended.  With a group of G lanes per tracklet, lane
+// sub = 0 of the group writes.
 template <int PA>
 __device__ __forceinline__ bool follow_step(FollowLane& f, const ClusterView& cl,
                                             const uint32_t* cblk, uint32_t nblk,
                                             const int32_t* upc, FollowOut& fo, const DevParams32* P,
-                                            const PV<float>& pv, float chi2max) {
+                                            const PV<float>& pv, float chi2max, uint32_t G = 1,
+                                            uint32_t sub = 0) {
   constexpr bool pa = PA == 1;
+  const bool lead = sub == 0;
   const int rn = f.r + (pa ? 1 : -1);
   if (rn >= NROW || rn < 0) return true;
   int32_t* H = fo.hits + (size_t)f.t * NROW;
@@ -697,14 +736,19 @@ __device__ __forceinline__ bool follow_step(FollowLane& f, const ClusterView& cl
   const int rn2 = rn + (pa ? 1 : -1);
   int32_t pre2 = -1;
   if (pa ? (rn2 < f.r1 + f.L && cand >= 0) : (rn2 >= f.r1 && rn2 >= 0)) pre2 = pa ? upc[cand] : H[rn2];
+  follow_flush(f, fo, lead);
   Trk<float>& k = f.k;
-  if (!propagate(k, row_dx<float>(P, f.r, rn), pv, true, pv.snp_max())) return true;
+  // the row's constants in one round of LDS reads, before the step
+  const float dx = row_dx<float>(P, f.r, rn);
+  const float vy = pv.vy(rn), vz = pv.vz(rn), edge = pv.hw(rn) + pv.edge_margin();
+  if (!propagate(k, dx, pv, true, pv.snp_max())) return true;
   ++f.n_steps;
+  const SInv<float> si = s_inverse(k, vy, vz);
   bool fresh = false;
   if (!known || (!pa && cand < 0)) {
-    if (fabsf(k.p[0]) > pv.hw(rn) + pv.edge_margin()) return true;
-    cand = search_row(cl, cblk, nblk, f.ubase + rn, k, f.anchor, pv.vy(rn), pv.vz(rn), chi2max,
-                      f.n_cands, q);
+    if (fabsf(k.p[0]) > edge) return true;
+    cand = search_row(cl, cblk, nblk, f.ubase + rn, k, f.anchor, vz, si, chi2max, f.n_cands, q, G,
+                      sub);
     fresh = true;
   }
   f.pre = pre2;
@@ -714,19 +758,26 @@ __device__ __forceinline__ bool follow_step(FollowLane& f, const ClusterView& cl
   if (pa) f.hi = rn;
   else if (first) f.lo = rn;
   if (cand < 0) {
-    if (first) H[rn] = -1;
+    if (first) {
+      f.pend_row = rn;
+      f.pend_hit = -1;
+    }
     if ((pa || rn < f.r1) && ++f.nmiss >= P->max_miss) return true;
     return false;
   }
   const float my = (float)q.x * (float)FX_SCALE;
   const float mz = (float)(q.y - f.anchor) * (float)FX_SCALE;
   ++f.n_upds;
-  if (!update(k, my, mz, pv.vy(rn), pv.vz(rn), (float*)nullptr)) {
-    if (first) H[rn] = -1;
+  if (!update(k, my, mz, si)) {
+    if (first) {
+      f.pend_row = rn;
+      f.pend_hit = -1;
+    }
     return true;
   }
   if (pa || fresh) {
-    H[rn] = cand;
+    f.pend_row = rn;
+    f.pend_hit = cand;
     ++f.nh;
   }
 #pragma unroll
@@ -811,6 +862,7 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
     if (PASS != FP_B) {
       while (!follow_step<1>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max)) {
       }
+      follow_flush(f, fo, true);
     }
     if (PASS == FP_A) {
       f.lo = f.r1;
@@ -819,6 +871,7 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
     } else if (follow_start_b(f, cl, fo, pv)) {
       while (!follow_step<0>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max)) {
       }
+      follow_flush(f, fo, true);
       follow_finish(f, fo);
     } else if (PASS == FP_AB) {
       follow_finish(f, fo);
@@ -856,6 +909,24 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
 // lanes compete for it: on a 2 ms Pb-Pb slice the two passes took 3.02, 2.53,
 // 2.41, 2.53 and 2.63 ms with 8, 12, 16, 20 and 24 waves per compute unit.
 #define FOLLOW_Q_WAVES_PER_CU 16
+// Few tracklets: a sort group that fills at most the lanes of
+// FOLLOW_SPREAD_WAVES waves (the resident grid of one group) has its tracklets
+// dealt evenly over those waves, one round, and each tracklet is held by a
+// group of up to FOLLOW_SPREAD_G lanes that search a row's candidates together.
+// A lone wave issues an instruction every ~7 cycles whatever its lanes hold, so
+// there the pass lasts as long as the instructions of the longest tracklet plus
+// what the wave's other lanes add (other branches, more candidates per search):
+// fewer tracklets per wave cost less per step, and idle SIMDs take the rest.
+// Following stage (both passes, sorts included), before -> after: 250 tracklets
+// 717 -> 512 us, 20,000 896 -> 597, 66,000 1071 -> 680, 178,000 1204 -> 1012.
+// Groups of 1 and 2 lanes at 20,000: 711 and 611 us (wider groups
+// have to agree through LDS and gained nothing); 128 and 256 waves per group at
+// 66,000: 1055 and 993 us, 512: 681.  Above 64 per wave (262,144 tracklets in
+// all) lanes are refilled from the queue instead: a 2 ms slice's 730,000 take
+// 2.37 ms there, and spreading them over more waves evicts lines (above).
+#define FOLLOW_SPREAD_WAVES 512
+#define FOLLOW_SPREAD_SLOTS 64
+#define FOLLOW_SPREAD_G 4
 template <int B, int PASS, bool COUNT>
 __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* __restrict__ cblk,
                                                  uint32_t nblk, const int32_t* __restrict__ upc,
@@ -876,22 +947,69 @@ __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* 
     if (COUNT && (threadIdx.x & 63) == 0) work[wave] = make_ulonglong4(0, 0, 0, 0);
     return;
   }
-  // FP32 only: the parameter block without its FP64 copies
-  __shared__ DevParams32 Ps;
-  const DevParams32* P = params_to_lds(Pg, &Ps);
-  const PV<float> pv{P};
   const uint32_t n_tl = scan_count(n_tl_dev, tl_cap);
-  const float chi2max = pv.chi2_max();
   // this workgroup's sort group: positions [gs, ge) of perm
   const uint32_t g = blockIdx.x % ngrp;
   const uint32_t npg = sort_blocks_per_group(n_tl, ngrp);
   const size_t gsz = (size_t)256 * npg;
   const uint32_t gs = npg ? bins[g * gsz] : 0u;
   const uint32_t ge = npg == 0 ? 0u : g + 1 < ngrp ? bins[(g + 1) * gsz] : n_tl;
+  // few tracklets: slots per wave and lanes per slot of the group's spread
+  const uint32_t wpb = B / 64, gw = gridDim.x / ngrp * wpb;
+  const uint32_t j0 = blockIdx.x / ngrp * wpb;
+  const uint32_t sw = gw < FOLLOW_SPREAD_WAVES ? gw : FOLLOW_SPREAD_WAVES;
+  const uint32_t per = (ge - gs + sw - 1) / sw;
+  const bool spread = per <= FOLLOW_SPREAD_SLOTS;
+  if (!COUNT && spread && j0 * per >= ge - gs) return;  // uniform per workgroup
+  // FP32 only: the parameter block without its FP64 copies
+  __shared__ DevParams32 Ps;
+  const DevParams32* P = params_to_lds(Pg, &Ps);
+  const PV<float> pv{P};
+  const float chi2max = pv.chi2_max();
   const uint64_t below = (1ull << (threadIdx.x & 63)) - 1ull;
   uint32_t w_steps = 0, w_cands = 0, w_upds = 0, w_iter = 0;
   FollowLane f;
-  bool busy = false, retired = false;
+  if (spread) {
+    uint32_t G = 1;
+    while (G < FOLLOW_SPREAD_G && per * (2 * G) <= 64) G *= 2;
+    const uint32_t lane = threadIdx.x & 63, sub = lane & (G - 1), slot = lane / G;
+    const bool lead = sub == 0;
+    const uint32_t i = gs + (j0 + (threadIdx.x >> 6)) * per + slot;
+    if (slot < per && i < ge) {
+      const uint32_t t = perm[i];
+      f.n_steps = f.n_cands = f.n_upds = 0;
+      bool busy = false;
+      if (PASS == FP_B) {
+        if (fo.ok[t]) {
+          follow_resume(f, t, cl, tl_start, tl_len, pts, fo);
+          busy = follow_start_b(f, cl, fo, pv);
+        }
+      } else {
+        busy = follow_init(f, t, cl, tl_start, tl_len, upc, pts, fo, P, pv, lead);
+        if (!busy && lead) key[t] = 0;
+      }
+      if (busy) {
+        while (!follow_step<PASS == FP_A ? 1 : 0>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max, G,
+                                                  sub)) {
+          if (COUNT) ++w_iter;
+        }
+        if (COUNT) ++w_iter;
+        follow_flush(f, fo, lead);
+        if (PASS == FP_A) f.lo = f.r1;
+        if (lead) {
+          follow_finish(f, fo);
+          if (PASS == FP_A) key[f.t] = (uint8_t)f.rs;
+        }
+      }
+      if (COUNT && lead) {
+        w_steps = f.n_steps;
+        w_cands = f.n_cands;
+        w_upds = f.n_upds;
+      }
+    }
+    if (COUNT) w_iter = (uint32_t)wave_max_i32((int32_t)w_iter);
+  }
+  bool busy = false, retired = spread;
   for (;;) {
     const uint64_t want = __ballot(!busy && !retired);
     const uint32_t nwant = (uint32_t)__popcll(want);
@@ -925,6 +1043,7 @@ __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* 
     if (COUNT) ++w_iter;
     if (busy && follow_step<PASS == FP_A ? 1 : 0>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max)) {
       busy = false;
+      follow_flush(f, fo, true);
       if (PASS == FP_A) {
         f.lo = f.r1;
         follow_finish(f, fo);

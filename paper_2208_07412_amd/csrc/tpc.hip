@@ -640,7 +640,12 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
           const int cap = FOLLOW_Q_WAVES_PER_CU / (Bv / 64);
           if (per_cu > cap) per_cu = cap;
           const uint32_t gq = ceil_div((uint32_t)(per_cu * c->n_cu), ng) * ng;
-          return gq < gf ? gq : gf;
+          // few tracklets are spread over more waves than would hold them
+          // (not when counting: the work counters are sized for gf)
+          uint32_t want = ceil_div(tcap < ng * FOLLOW_SPREAD_WAVES ? tcap : ng * FOLLOW_SPREAD_WAVES,
+                                   (uint32_t)(Bv / 64) * ng) * ng;
+          if (Cv || want < gf) want = gf;
+          return gq < want ? gq : want;
         };
         const uint32_t refill = FOLLOW_REFILL;
         sort_by_key(ng);
