@@ -73,9 +73,10 @@ __device__ __forceinline__ void latch_capacity(DevStatus* st, int kind, uint32_t
   latch(st, TPC_ERR_CAPACITY, required);
 }
 
-__device__ __forceinline__ bool failed(const DevStatus* st) {
-  return __atomic_load_n(&st->status, __ATOMIC_RELAXED) != 0;
-}
+// An error latched by an earlier launch (a plain load: what this launch
+// latches itself need not be seen, and an atomic load would go past the caches
+// at the start of every workgroup).
+__device__ __forceinline__ bool failed(const DevStatus* st) { return st->status != 0; }
 
 __device__ __forceinline__ int64_t floor_div64(int64_t a, int64_t b) {  // b > 0
   int64_t q = a / b;

@@ -638,78 +638,179 @@ __global__ __launch_bounds__(64) void k_cluster_peaks_list(ZsArgs in,
 }
 
 // ------------------------------------------------------------ shared-tile pass
-// The per-window pass is bound by the latency of its dependent LDS and memory
-// steps rather than by issue: its time follows the number of windows in
-// flight per compute unit, which the tile's LDS limits (one tile per wave).
-// Here NW waves (the library launches two) share the tile of one window of W
-// bins: each wave takes every NW-th 64-sample step of the window, so a
+// NW waves (the library launches two) share the tile of one window of W bins:
+// each wave takes a contiguous part of the window's 64-sample steps, so a
 // compute unit holds NW times as many waves for the same tile, and longer
 // windows recompute less halo per core sample.  The phases of a window are
-// ordered by workgroup barriers (four per window when one moment batch
-// suffices), whose waits take back most of what the extra waves gain.  The
-// results are those of the per-window pass.
+// ordered by workgroup barriers (four per window when one batch of peaks
+// suffices).
 //
-// Tile cell: ADC in bits 0-9; v = bits 10-15 is a non-peak's up code
-// (v <= 10) or, for a peak, MW_V0 + its moment slot (v <= 61); v = MW_PEND
-// marks a core peak still waiting for a slot, v = MW_NONE a peak with no
-// record to write here (outside the core, or already written).  Each wave
-// owns MW_SW(NW) slots and hands them out in its own sample order, so no slot
-// counter is shared.
-#define MW_V0 11
-#define MW_PEND 62
-#define MW_NONE 63
-#define MW_SW(NW) (51 / (NW))  // slots per wave (NW * MW_SW <= 51)
-// 64-sample steps of a window (core and halo) that a valid input can fill:
-// at most one sample per cell, at most 138 pads
-#define MW_GROUPS(W) ((((W) + 2 * CL_HALO) * (CL_TP - 4) + 63) / 64)
+// Bound by instruction issue: on a 2 ms Pb-Pb slice (2.3e8 samples, 1.7e7
+// clusters) 1.60 ms at 32 bins and 8 windows per workgroup, 2.96 ms before the
+// peaks gathered their moments, the prefetch was left in flight and the steps
+// lost their lane masks.  In turn: gathered moments 2.30 ms; loads that nothing
+// waits for before their use, and one index load per chunk, 1.89; straight-line
+// steps and ranks without per-step counts 1.63.  Windows of 24 bins 2.3 ms
+// (before the last step), one wave per window of 24 bins 1.73, three and four
+// waves 2.1 and 2.8; workgroups that stay and walk chunk after chunk 2.7.
+//
+// The moments are gathered at the peaks: a peak's 25 cells hold all samples
+// that reach it in two uphill steps, so five lanes per peak (one per time bin,
+// twelve peaks per wave step) read five cells each, decide membership from the
+// up codes alone and add up.  A window of 32 bins at the 4% occupancy of a 2 ms
+// Pb-Pb slice has ~166 samples (with the halo) but ~10 peaks: one gather step,
+// where a pass in which every sample chases its peak and adds itself to it with
+// two 64-bit LDS atomics takes three, each of them longer.
+//
+// Tile cell: the up code in bits 0-3 and the ADC in bits 4-13, so that the
+// three cells of a row become keys (adc, time, pad) with one and-or each.  The
+// up code of a step (dt, dp) is 5 (dt + 1) + dp + 1 (6 = itself): the codes
+// order the nine cells by (time, pad), and adding one to the bit position
+// MW_POS + 5 dt + dp - 6 of a cell (dt, dp) bins and pads from the peak gives the
+// bit position of the cell it points at.
+//
+// A step's lanes without a sample in the tile work on a cell of their own
+// behind the tile, and samples in the outermost rows get codes that nothing
+// reads: each phase of a step is straight-line code without lane masks.
+#define MW_SELF 6
+#define MW_POS 16       // bit of the peak's own cell in a mask of reached cells
+#define MW_LIST 48      // peaks listed per wave and batch
+#define MW_GATHER 12    // peaks per gather step of a wave, 5 lanes each
+#define MW_GUARD 144    // cells read before and behind the tile (a row and two)
+// samples of a window (core and halo) that a valid input can have: at most one
+// per cell, at most 138 pads
+#define MW_MAXS(W) (((W) + 2 * CL_HALO) * (CL_TP - 4))
 
-__device__ __forceinline__ int mw_code(int cell) {
-  const int v = cell >> 10;
-  return v <= 10 ? v : 5;
+// tile offset of the cell an up code points at
+__device__ __forceinline__ int mw_offset(int code) {
+  const int r = code >= 10 ? 2 : code >= 5 ? 1 : 0;
+  return (r - 1) * CL_TP + (code - 5 * r - 1);
 }
-__device__ __forceinline__ int mw_cell(int a, int v) { return a | (v << 10); }
 
+// One array: moment sums | tile | the idle lanes' cell (column 2 of the row
+// behind) | peak lists and counts.  The sums and the lists are also the guards
+// that codes of the outermost rows and of the idle cell read (a row and two
+// cells on each side; nothing uses what comes of them).  11,488 bytes at W = 32:
+// a fourteenth workgroup per compute unit fits.
+// One array: moment sums | tile | the idle lanes' cell (column 2 of the row
+// behind) | peak lists and counts.  The sums and the lists are also the guards
+// that codes of the outermost rows and of the idle cell read (a row and two
+// cells on each side; nothing uses what comes of them).  11,488 bytes at W = 32:
+// a fourteenth workgroup per compute unit fits.
 template <int W, int NW>
 struct PeaksLdsMw {
-  __attribute__((aligned(16))) uint16_t tile[(W + 2 * CL_TH) * CL_TP];
-  unsigned long long acc0[NW * MW_SW(NW)], acc1[NW * MW_SW(NW)];
-  uint32_t grp[MW_GROUPS(W) + 1];  // core peaks per 64-sample step (ranks sum them)
-  uint16_t pk_cell[NW * MW_SW(NW)];
-  uint16_t pk_gi[NW * MW_SW(NW)];  // step << 6 | rank within the step
-  uint16_t pk_a[NW * MW_SW(NW)];   // the peak's ADC
-  uint32_t wcnt[NW];               // slots used by each wave in the batch
+  static constexpr int TILE0 = 8 * NW * MW_GATHER >= MW_GUARD ? 8 * NW * MW_GATHER : MW_GUARD;
+  static constexpr int TILE = ((W + 2 * CL_TH) * CL_TP + 7) / 8 * 8;
+  static constexpr int LIST0 = TILE0 + TILE + 8;
+  static constexpr int COUNT0 = LIST0 + NW * MW_LIST;
+  static constexpr int END = COUNT0 + 2 * NW > LIST0 + MW_GUARD ? COUNT0 + 2 * NW : LIST0 + MW_GUARD;
+  static_assert(TILE0 % 8 == 0 && COUNT0 % 2 == 0, "aligned parts");
+  __attribute__((aligned(16))) uint16_t raw[END];
+  __device__ unsigned long long* acc0() { return reinterpret_cast<unsigned long long*>(raw); }
+  __device__ unsigned long long* acc1() { return acc0() + NW * MW_GATHER; }
+  __device__ uint16_t* tile() { return raw + TILE0; }
+  __device__ uint16_t* list() { return raw + LIST0; }  // core peaks of each wave: cells
+  __device__ uint32_t* count() { return reinterpret_cast<uint32_t*>(raw + COUNT0); }
 };
 
-template <int PRE, int NT>
-__device__ __forceinline__ void prefetch_mw(const ZsArgs& in, const WinRange& R,
-                                            SampleRegs<PRE>& S) {
+// The samples of a wave's steps of one window, as loaded (nothing is computed
+// from them before their use, so the loads stay in flight meanwhile).
+template <int PRE>
+struct MwRegs {
+  uint16_t t[PRE], p[PRE], a[PRE];
+};
+
+// Raw buffers over a chunk's samples: the lane's offset is constant and a
+// step's first sample is a scalar, so a load costs no vector address.
+struct MwBufs {
+  __amdgpu_buffer_rsrc_t time, pad, adc;
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t mw_buffer(const uint16_t* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), (short)0, (int)0xFFFFFFFF,
+                                           0x00020000);
+}
+
+// A wave's samples [first, end) of the window [s_lo, s_hi): a contiguous run
+// of 64-sample steps, in wave order.
+struct MwShare {
+  uint32_t first, end;
+};
+template <int NW>
+__device__ __forceinline__ MwShare mw_share(const WinRange& R, uint32_t wave) {
+  const uint32_t len = (R.s_hi - R.s_lo + 64 * NW - 1) / (64 * NW) * 64;
+  MwShare h;
+  h.first = R.s_lo + wave * len;
+  h.end = min(h.first + len, R.s_hi);
+  return h;
+}
+
+// Loads the wave's first PRE steps (base: the sample the buffers begin at);
+// lanes past its samples load nothing.
+template <int PRE>
+__device__ __forceinline__ void prefetch_mw(const MwBufs& B, uint32_t base, MwShare h,
+                                            uint32_t lane, MwRegs<PRE>& S) {
 #pragma unroll
   for (int j = 0; j < PRE; ++j) {
-    const uint32_t s = R.s_lo + threadIdx.x + j * NT;
-    if (s < R.s_hi) {
-      S.tp[j] = ((uint32_t)in.time[s] << 16) | in.pad[s];
-      S.a[j] = in.adc[s];
-    } else {
-      S.tp[j] = 0xFFFFFFFFu;
-      S.a[j] = 0;
+    const uint32_t s0 = h.first + j * 64;
+    if (s0 < h.end) {
+      if (lane < h.end - s0) {
+        const int off = (int)((s0 - base) * 2u);
+        S.t[j] = __builtin_amdgcn_raw_buffer_load_b16(B.time, (int)(lane * 2u), off, 0);
+        S.p[j] = __builtin_amdgcn_raw_buffer_load_b16(B.pad, (int)(lane * 2u), off, 0);
+        S.a[j] = __builtin_amdgcn_raw_buffer_load_b16(B.adc, (int)(lane * 2u), off, 0);
+      }
     }
   }
 }
 
-template <int ROWS, int PRE, int NT>
-__device__ __forceinline__ void scatter_mw(uint16_t* tile, const ZsArgs& in, const WinRange& R,
-                                           const SampleRegs<PRE>& S, int tile_t0, int np,
-                                           bool place) {
-#pragma unroll
-  for (int j = 0; j < PRE; ++j) {
-    const int c = cell_of<ROWS>(S.tp[j], tile_t0, np);
-    if (c >= 0) tile[c] = place ? (uint16_t)(S.a[j] & 0x3FF) : 0;
-  }
-  for (uint32_t s = R.s_lo + PRE * NT + threadIdx.x; s < R.s_hi; s += NT) {
-    const uint32_t tp = ((uint32_t)in.time[s] << 16) | in.pad[s];
-    const int c = cell_of<ROWS>(tp, tile_t0, np);
-    if (c >= 0) tile[c] = place ? (uint16_t)(in.adc[s] & 0x3FF) : 0;
-  }
+// Waits for every load (vmcnt 0).  Ends the rare paths that load samples
+// outside the prefetch: without it the compiler, which cannot tell whether
+// such a path ran, waits for all loads, the next window's prefetch among them,
+// at the first use of the registers that the path loaded into.
+__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// Window i of a chunk from the chunk's index entries (see peaks_chunk_mw).
+__device__ __forceinline__ WinRange mw_range(uint32_t ent, int i) {
+  WinRange R;
+  R.s_lo = (uint32_t)__builtin_amdgcn_readlane((int)ent, 3 * i);
+  R.c_lo = (uint32_t)__builtin_amdgcn_readlane((int)ent, 3 * i + 1);
+  R.c_hi = max((uint32_t)__builtin_amdgcn_readlane((int)ent, 3 * i + 4), R.c_lo);
+  R.s_hi = max((uint32_t)__builtin_amdgcn_readlane((int)ent, 3 * i + 5), R.s_lo);
+  return R;
+}
+
+// A sample's tile cell; the idle cell outside the tile or the row.
+template <int W>
+__device__ __forceinline__ uint32_t mw_cell_of(uint32_t t, uint32_t p, int tile_t0, int np,
+                                               bool here) {
+  constexpr uint32_t ROWS = W + 2 * CL_TH;
+  const uint32_t lt = t - (uint32_t)tile_t0;
+  const bool in = here && lt < ROWS && p < (uint32_t)np;
+  return in ? __umul24(lt, CL_TP) + p + 2 : ROWS * CL_TP + 2;
+}
+template <int W>
+__device__ __forceinline__ bool mw_core(uint32_t c) {
+  return c - CL_TH * CL_TP < (uint32_t)(W * CL_TP);
+}
+
+// The largest key adc << 4 | code over a sample's cell c and its neighbours
+// (an empty cell's key stays below 16); own = the sample's own key.
+__device__ __forceinline__ uint32_t mw_up_key(const uint16_t* tile, int c, uint32_t& own) {
+  const int w = (c - 1) >> 1;
+  const uint32_t sh = ((c - 1) & 1) * 16;
+  const uint32_t* t = reinterpret_cast<const uint32_t*>(tile) + w - CL_TP / 2;
+  const uint32_t u0 = t[0], u1 = t[1];
+  const uint32_t m0 = t[CL_TP / 2], m1 = t[CL_TP / 2 + 1];
+  const uint32_t d0 = t[CL_TP], d1 = t[CL_TP + 1];
+  const uint32_t ul = (__builtin_amdgcn_alignbit(u1, u0, sh) & 0x3FF03FF0u) | 0x00010000u;
+  const uint32_t ml = (__builtin_amdgcn_alignbit(m1, m0, sh) & 0x3FF03FF0u) | 0x00060005u;
+  const uint32_t dl = (__builtin_amdgcn_alignbit(d1, d0, sh) & 0x3FF03FF0u) | 0x000B000Au;
+  const uint32_t uh = ((u1 >> sh) & 0x3FF0u) | 2u;
+  const uint32_t mh = ((m1 >> sh) & 0x3FF0u) | 7u;
+  const uint32_t dh = ((d1 >> sh) & 0x3FF0u) | 12u;
+  own = ml >> 16;
+  const uint32_t lo = pk_max_u16(pk_max_u16(ul, ml), dl);
+  return max(max(lo & 0xFFFFu, lo >> 16), max(max(uh, mh), dh));
 }
 
 template <int W, int K, int NW, int PRE>
@@ -720,198 +821,254 @@ __device__ __forceinline__ void peaks_chunk_mw(const ZsArgs& in, const uint32_t*
                                                int32_t* __restrict__ sample_label,
                                                const DevParams* __restrict__ P, DevStatus* st,
                                                uint32_t logical, PeaksLdsMw<W, NW>& L) {
-  constexpr int ROWS = W + 2 * CL_TH, NT = 64 * NW, SW = MW_SW(NW);
-  uint16_t* tile = L.tile;
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int NT = 64 * NW;
+  using Lds = PeaksLdsMw<W, NW>;
+  uint16_t* const tile = L.tile();
+  const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
   const uint64_t below = (1ull << lane) - 1ull;
   const uint32_t ur = logical / nchunk, chunk = logical % nchunk;
   if (ur >= n_ur) return;
-  const int np = uni(P->np[ur % NROW]), qmin = uni(P->qmax_min);
   const uint32_t* zb = zblk + (size_t)ur * (nblk + 1);
-  uint32_t rs0 = uni(zb[0]), rs1 = uni(zb[nblk]);
-  if (rs1 > in.n_samples) rs1 = in.n_samples;
-  if (rs0 > rs1) rs0 = rs1;
   const int w0 = chunk * K;
   const int w1 = min((int)nwin, w0 + K);
-  for (int i = threadIdx.x; i < ROWS * CL_TP / 8; i += NT)
-    reinterpret_cast<uint4*>(tile)[i] = make_uint4(0, 0, 0, 0);
-  for (int i = ROWS * CL_TP / 8 * 8 + threadIdx.x; i < ROWS * CL_TP; i += NT) tile[i] = 0;
-  if (threadIdx.x < NW * SW) {
-    L.acc0[threadIdx.x] = 0;
-    L.acc1[threadIdx.x] = 0;
+  // the chunk's index entries in one load, one per lane, read back as scalars:
+  // of window i (and one past the last) the entries a halo before its first
+  // bin, at its first bin and a halo after it; in the last lanes the row's ends
+  static_assert(3 * (K + 1) <= 62 && CL_HALO == 1 << CL_BSHIFT, "entries of a chunk fit one wave");
+  uint32_t ent;
+  {
+    const int i = (int)(lane / 3), o = (int)(lane - 3 * (lane / 3)) - 1;
+    const int b = lane == 62 ? 0 : lane == 63 ? (int)nblk : (w0 + i) * (W >> CL_BSHIFT) + o;
+    ent = zb[min(max(b, 0), (int)nblk)];
   }
-  WinRange R = window_range<W>(zb, nblk, w0, rs0, rs1);
-  SampleRegs<PRE> cur, nxt;
-  prefetch_mw<PRE, NT>(in, R, cur);
+  const int np = uni(P->np[ur % NROW]);
+  // the least key of a peak: ADCs have 10 bits, so a higher cut passes none
+  const uint32_t qmin16 = (uint32_t)min(uni(P->qmax_min), 1024) << 4;
+  // clear everything (16-byte words, then the rest)
+  for (int i = threadIdx.x; i < Lds::END / 8; i += NT)
+    reinterpret_cast<uint4*>(L.raw)[i] = make_uint4(0, 0, 0, 0);
+  for (int i = Lds::END / 8 * 8 + threadIdx.x; i < Lds::END; i += NT) L.raw[i] = 0;
+  uint32_t rs0 = (uint32_t)__builtin_amdgcn_readlane((int)ent, 62);
+  uint32_t rs1 = (uint32_t)__builtin_amdgcn_readlane((int)ent, 63);
+  if (rs1 > in.n_samples) rs1 = in.n_samples;
+  if (rs0 > rs1) rs0 = rs1;
+  ent = min(max(ent, rs0), rs1);
+  WinRange R = mw_range(ent, 0);
+  MwShare h = mw_share<NW>(R, wave);
+  const uint32_t base = R.s_lo;
+  const MwBufs bufs{mw_buffer(in.time + base), mw_buffer(in.pad + base), mw_buffer(in.adc + base)};
+  MwRegs<PRE> nxt;
+  prefetch_mw<PRE>(bufs, base, h, lane, nxt);
+  // this lane's peak of a gather step and its time bin relative to the peak
+  const uint32_t pg = lane / 5;
+  const int dr = (int)(lane - 5 * pg) - 2;
+  unsigned long long* const acc0 = L.acc0() + wave * MW_GATHER + pg;
+  unsigned long long* const acc1 = L.acc1() + wave * MW_GATHER + pg;
+  uint16_t* const my_list = L.list() + wave * MW_LIST;
   __syncthreads();
   for (int w = w0; w < w1; ++w) {
     const int tile_t0 = w * W - CL_TH;
-    scatter_mw<ROWS, PRE, NT>(tile, in, R, cur, tile_t0, np, true);
+    const bool dense = h.first + PRE * 64 < h.end;  // steps beyond the prefetch (uniform)
+    // this lane's cell in the step that begins at s0, beyond the prefetch
+    auto load_cell = [&](uint32_t s0, uint32_t* adc) {
+      const uint32_t s = s0 + lane;
+      uint32_t t = 0, p = 0;
+      if (s < h.end) {
+        t = in.time[s];
+        p = in.pad[s];
+        if (adc) *adc = in.adc[s];
+      }
+      return mw_cell_of<W>(t, p, tile_t0, np, s < h.end);
+    };
+    uint32_t cell[PRE];
+#pragma unroll
+    for (int j = 0; j < PRE; ++j) {
+      const uint32_t s0 = h.first + j * 64;
+      if (s0 < h.end) {
+        cell[j] = mw_cell_of<W>(nxt.t[j], nxt.p[j], tile_t0, np, lane < h.end - s0);
+        tile[cell[j]] = (uint16_t)(nxt.a[j] << 4);
+      }
+    }
+    if (dense) {
+      for (uint32_t s0 = h.first + PRE * 64; s0 < h.end; s0 += 64) {
+        uint32_t a = 0;
+        const uint32_t c = load_cell(s0, &a);
+        tile[c] = (uint16_t)(a << 4);
+      }
+      loads_done();
+    }
     WinRange Rn = R;
+    MwShare hn = h;
     if (w + 1 < w1) {
-      Rn = window_range<W>(zb, nblk, w + 1, rs0, rs1);
-      prefetch_mw<PRE, NT>(in, Rn, nxt);
+      Rn = mw_range(ent, w + 1 - w0);
+      hn = mw_share<NW>(Rn, wave);
+      prefetch_mw<PRE>(bufs, base, hn, lane, nxt);
     }
     __syncthreads();
     // more samples than cells: not a valid input (uniform over the workgroup)
-    const bool fits = R.s_hi - R.s_lo <= (uint32_t)MW_GROUPS(W) * 64u;
+    const bool fits = R.s_hi - R.s_lo <= (uint32_t)MW_MAXS(W);
     if (!fits && threadIdx.x == 0) latch(st, TPC_ERR_INPUT);
     uint32_t total = 0;
     if (fits) {
-      // up codes of the samples within 2 bins of the core, in place; each
-      // wave gives its core peaks its own slots in sample order
+      // up codes in place; each wave lists its core peaks in sample order
       uint32_t used = 0;
-      uint32_t j = 0;
-      for (uint32_t s0 = R.s_lo + wave * 64; s0 < R.s_hi; s0 += NT, ++j) {
-        const uint32_t s = s0 + lane;
-        int c = -1, lt = -1;
-        if (s < R.s_hi) {
-          const uint32_t tp = sample_tp(in, cur, j, s);
-          c = cell_of<ROWS>(tp, tile_t0, np);
-          lt = (int)(tp >> 16) - tile_t0;
-        }
-        const bool live = c >= 0 && lt >= CL_TH - 2 && lt < CL_TH + W + 2;
-        int a = 0;
-        const int code = live ? up_code_of(tile, c, qmin, a) : 0;
-        const bool pk = live && (code & 16) && lt >= CL_TH && lt < CL_TH + W;
+      auto list = [&](bool pk, uint32_t c, uint32_t from) {
         const uint64_t m = __ballot(pk);
-        const uint32_t idx = (uint32_t)__popcll(m & below);
-        const uint32_t k = used + idx;
-        const bool pslot = pk && k < (uint32_t)SW;
-        const uint32_t slot = wave * SW + k;
-        const int v = (code & 16) ? (pk ? (pslot ? MW_V0 + (int)slot : MW_PEND) : MW_NONE)
-                                  : (code & 15);
-        if (live) tile[c] = (uint16_t)mw_cell(a, v);
-        const uint32_t g = (s0 - R.s_lo) >> 6;
-        if (pslot) {
-          L.pk_cell[slot] = (uint16_t)c;
-          L.pk_a[slot] = (uint16_t)a;
-          L.pk_gi[slot] = (uint16_t)((g << 6) | idx);
-        }
-        if (lane == 0) L.grp[g] = (uint32_t)__popcll(m);
+        const uint32_t k = used + (uint32_t)__popcll(m & below) - from;
+        if (pk && k < MW_LIST) my_list[k] = (uint16_t)c;
         used += (uint32_t)__popcll(m);
+      };
+      auto code_step = [&](uint32_t c) {
+        uint32_t own;
+        const uint32_t best = mw_up_key(tile, (int)c, own);
+        tile[c] = (uint16_t)((own & 0x3FF0u) | (best & 15u));
+        list(best == own && own >= qmin16 && mw_core<W>(c), c, 0);
+      };
+#pragma unroll
+      for (int j = 0; j < PRE; ++j)
+        if (h.first + j * 64 < h.end) code_step(cell[j]);
+      if (dense) {
+        for (uint32_t s0 = h.first + PRE * 64; s0 < h.end; s0 += 64)
+          code_step(load_cell(s0, nullptr));
+        loads_done();
       }
-      if (lane == 0) L.wcnt[wave] = min(used, (uint32_t)SW);
+      if (lane == 0) L.count()[wave] = used;
       __syncthreads();
-      const uint32_t ng = (R.s_hi - R.s_lo + 63) >> 6;
-      for (uint32_t g = 0; g < ng; ++g) total += L.grp[g];
+      uint32_t cnt[NW];
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        cnt[q] = uni(L.count()[q]);
+        total += cnt[q];
+      }
       ClusterRec* wrec = rec + R.c_lo;
-      uint32_t nb = 0;
+      for (uint32_t from = 0;;) {
+        // the listed peaks of all waves, twelve per step of a wave
+        uint32_t n[NW], nb = 0;
+        bool more = false;
 #pragma unroll
-      for (int q = 0; q < NW; ++q) nb += L.wcnt[q];
-      uint32_t done = 0;
-      // the moment sums start at zero: cleared at the start and by each record
-      while (nb > 0) {
-        // every sample within two bins of the core adds itself to the core
-        // peak that two uphill steps reach
-        j = 0;
-        for (uint32_t s0 = R.s_lo + wave * 64; s0 < R.s_hi; s0 += NT, ++j) {
-          const uint32_t s = s0 + lane;
-          if (s >= R.s_hi) continue;
-          const uint32_t tp = sample_tp(in, cur, j, s);
-          const int x = cell_of<ROWS>(tp, tile_t0, np);
-          const int lt = (int)(tp >> 16) - tile_t0;
-          if (x < 0 || lt < CL_TH - 2 || lt >= CL_TH + W + 2) continue;
-          const int tx = tile[x];
-          const int cx = mw_code(tx);
-          const int ly = lt + (cx >> 2) - 1;
-          if (ly < CL_TH - 1 || ly >= CL_TH + W + 1) continue;
-          const int y = x + code_offset(cx);
-          const int cy = mw_code(tile[y]);
-          const int vz = tile[y + code_offset(cy)] >> 10;
-          if (vz < MW_V0 || vz >= MW_V0 + NW * SW) continue;
-          const int slot = vz - MW_V0;
-          const uint32_t a = tx & 0x3FF;
-          const uint32_t dt2 = 4 - (cx >> 2) - (cy >> 2);  // dt + 2, dt = sample - peak
-          const uint32_t dp2 = 4 - (cx & 3) - (cy & 3);
-          const int dt = (int)dt2 - 2, dp = (int)dp2 - 2;
-          const uint32_t dtt = (uint32_t)__mul24(dt, dt), dpp = (uint32_t)__mul24(dp, dp);
-          const uint32_t ap = __umul24(a, dp2), at = __umul24(a, dt2);
-          const uint32_t lo0 = a | (1u << 15) | ((uint32_t)(a >= 1023) << 20) | (ap << 25);
-          uint32_t adpp;
-          asm("v_mul_u32_u24 %0, %1, %2" : "=v"(adpp) : "v"(a), "v"(dpp));
-          const uint32_t hi0 = (ap >> 7) | (adpp << 10);
-          const uint64_t v0 = ((uint64_t)hi0 << 32) | lo0;
-          const uint64_t v1 = ((uint64_t)__umul24(a, dtt) << 32) | at;
-          atomicAdd(&L.acc0[slot], (unsigned long long)v0);
-          atomicAdd(&L.acc1[slot], (unsigned long long)v1);
+        for (int q = 0; q < NW; ++q) {
+          n[q] = cnt[q] > from ? min(cnt[q] - from, (uint32_t)MW_LIST) : 0u;
+          more = more || cnt[q] > from + MW_LIST;
+          nb += n[q];
         }
-        __syncthreads();
-        // the batch's records, at the peak's rank in the window; the tile
-        // is read again only if another batch follows
-        const bool more = done + nb < total;
-        if (threadIdx.x < NW * SW && threadIdx.x % SW < L.wcnt[threadIdx.x / SW]) {
-          const int c = L.pk_cell[threadIdx.x];
-          const uint32_t gi = L.pk_gi[threadIdx.x];
-          uint32_t rank = gi & 63;
-          for (uint32_t g = 0; g < (gi >> 6); ++g) rank += L.grp[g];
-          const int lt = c / CL_TP;
-          const uint64_t meta = (uint64_t)(uint32_t)(c - lt * CL_TP - 2) |
-                                ((uint64_t)(uint32_t)(lt + tile_t0) << 8) |
-                                ((uint64_t)L.pk_a[threadIdx.x] << 32);
-          ClusterRec rr;
-          rr.m0 = L.acc0[threadIdx.x];
-          rr.m1 = L.acc1[threadIdx.x];
-          rr.m2 = meta;
-          wrec[rank] = rr;
-          L.acc0[threadIdx.x] = 0;
-          L.acc1[threadIdx.x] = 0;
-          if (more) tile[c] = (uint16_t)mw_cell(L.pk_a[threadIdx.x], MW_NONE);
-        }
-        done += nb;
-        if (!more) break;
-        __syncthreads();
-        // slots for the core peaks still waiting, each wave in its sample order
-        used = 0;
-        j = 0;
-        for (uint32_t s0 = R.s_lo + wave * 64; s0 < R.c_hi; s0 += NT, ++j) {
-          const uint32_t s = s0 + lane;
-          int c = -1;
-          if (s >= R.c_lo && s < R.c_hi) c = cell_of<ROWS>(sample_tp(in, cur, j, s), tile_t0, np);
-          const int cell = c >= 0 ? tile[c] : 0;
-          const int v = cell >> 10;
-          const bool pk = v >= MW_V0;  // a peak in the core
-          const bool pend = v == MW_PEND;
-          const uint64_t m = __ballot(pk), mp = __ballot(pend);
-          const uint32_t k = used + (uint32_t)__popcll(mp & below);
-          if (pend && k < (uint32_t)SW) {
-            const uint32_t slot = wave * SW + k;
-            tile[c] = (uint16_t)mw_cell(cell & 0x3FF, MW_V0 + (int)slot);
-            L.pk_cell[slot] = (uint16_t)c;
-            L.pk_a[slot] = (uint16_t)(cell & 0x3FF);
-            L.pk_gi[slot] = (uint16_t)((((s0 - R.s_lo) >> 6) << 6) | (uint32_t)__popcll(m & below));
+        for (uint32_t e0 = wave * MW_GATHER; e0 < nb; e0 += NW * MW_GATHER) {
+          const bool on = pg < MW_GATHER && e0 + pg < nb;
+          const uint32_t e = on ? e0 + pg : e0;
+          // its place in the lists, and the rank of the peak in the window
+          uint32_t slot = e, rank = e + from, listed = n[0], ahead = cnt[0];
+#pragma unroll
+          for (int q = 1; q < NW; ++q) {
+            if (e >= listed) {
+              slot = e + (q * MW_LIST - listed);
+              rank = e + (from + ahead - listed);
+            }
+            listed += n[q];
+            ahead += cnt[q];
           }
-          used += (uint32_t)__popcll(mp);
-        }
-        if (lane == 0) L.wcnt[wave] = min(used, (uint32_t)SW);
-        __syncthreads();
-        nb = 0;
+          const int c = L.list()[slot];
+          // the five cells of this lane's time bin, pads -2..2 of the peak's
+          const int x = c + dr * CL_TP - 2;
+          const uint32_t* t = reinterpret_cast<const uint32_t*>(tile) + (x >> 1);
+          const uint32_t sh = (x & 1) * 16;
+          const uint32_t x0 = t[0], x1 = t[1], x2 = t[2];
+          const uint32_t v01 = __builtin_amdgcn_alignbit(x1, x0, sh);
+          const uint32_t v23 = __builtin_amdgcn_alignbit(x2, x1, sh);
+          const uint32_t v4 = x2 >> sh;
+          // bit positions of the cells that these five point at
+          const int y0 = MW_POS - MW_SELF + 5 * dr - 2;
+          const uint32_t y[5] = {y0 + (v01 & 15u), y0 + 1 + ((v01 >> 16) & 15u), y0 + 2 + (v23 & 15u),
+                                 y0 + 3 + ((v23 >> 16) & 15u), y0 + 4 + (v4 & 15u)};
+          // the cells next to the peak that point at it (and the peak itself),
+          // as a mask over bit positions: all other positions of a cell's
+          // target, taken modulo 32, are clear bits
+          uint32_t reach = 0;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) nb += L.wcnt[q];
+          for (int i = 1; i <= 3; ++i) {
+            const uint64_t at = __ballot(y[i] == MW_POS);
+            const uint32_t m3 = (uint32_t)(at >> (5 * pg + 1)) & 7u;  // bins -1, 0, 1
+            reach |= (__umul24(m3, 0x111u) & 0x421u) << (MW_POS - 7 + i);
+          }
+          uint32_t a[5] = {(v01 >> 4) & 0x3FFu, (v01 >> 20) & 0x3FFu, (v23 >> 4) & 0x3FFu,
+                           (v23 >> 20) & 0x3FFu, (v4 >> 4) & 0x3FFu};
+          const uint32_t qmax = a[2];
+          uint32_t n5 = 0;
+#pragma unroll
+          for (int i = 0; i < 5; ++i) {
+            a[i] &= (uint32_t)__builtin_amdgcn_sbfe((int)reach, y[i], 1);
+            n5 += min(a[i], 1u);
+          }
+          const uint32_t top = max(max(max(a[0], a[1]), max(a[2], a[3])), a[4]);
+          const uint32_t s1 = a[0] + a[4], s2 = a[1] + a[3], q5 = a[2] + s1 + s2;
+          const uint32_t sp2 = a[1] + 2 * a[2] + 3 * a[3] + 4 * a[4], spp = 4 * s1 + s2;
+          if (on) {
+            const uint32_t lo0 = q5 | (n5 << 15) | ((uint32_t)(top >= 1023u) << 20) | (sp2 << 25);
+            const uint32_t hi0 = (sp2 >> 7) | (spp << 10);
+            atomicAdd(acc0, ((unsigned long long)hi0 << 32) | lo0);
+            atomicAdd(acc1,
+                      ((unsigned long long)__umul24(q5, (uint32_t)(dr * dr)) << 32) |
+                          __umul24(q5, (uint32_t)(dr + 2)));
+          }
+          wave_sync();  // a peak's five lanes belong to one wave
+          if (on && dr == 0) {
+            const int lt = c / CL_TP;
+            ClusterRec rr;
+            rr.m0 = *acc0;
+            rr.m1 = *acc1;
+            rr.m2 = (uint64_t)(uint32_t)(c - lt * CL_TP - 2) |
+                    ((uint64_t)(uint32_t)(lt + tile_t0) << 8) | ((uint64_t)qmax << 32);
+            wrec[rank] = rr;
+            *acc0 = 0;
+            *acc1 = 0;
+          }
+          wave_sync();
+        }
+        if (!more) break;
+        // the next peaks of each wave's sample order
+        from += MW_LIST;
+        __syncthreads();
+        used = 0;
+        auto list_step = [&](uint32_t c) {
+          const uint32_t own = tile[c];
+          list((own & 15u) == MW_SELF && own >= qmin16 && mw_core<W>(c), c, from);
+        };
+#pragma unroll
+        for (int j = 0; j < PRE; ++j)
+          if (h.first + j * 64 < h.end) list_step(cell[j]);
+        if (dense) {
+          for (uint32_t s0 = h.first + PRE * 64; s0 < h.end; s0 += 64)
+            list_step(load_cell(s0, nullptr));
+          loads_done();
+        }
+        __syncthreads();
       }
     }
     if (threadIdx.x == 0) win_cnt[(size_t)ur * nwin + w] = total;
     if (sample_label && fits) {
-      // the tile is final: the last batch wrote none of it
       for (uint32_t s = R.c_lo + threadIdx.x; s < R.c_hi; s += NT) {
-        const uint32_t tp = ((uint32_t)in.time[s] << 16) | in.pad[s];
-        const int lt = (int)(tp >> 16) - tile_t0;
-        const int x = cell_of<ROWS>(tp, tile_t0, np);
+        const uint32_t c = mw_cell_of<W>(in.time[s], in.pad[s], tile_t0, np, true);
         int32_t lab = -1;
-        if (x >= 0 && lt >= CL_TH && lt < CL_TH + W) {
-          const int y = x + code_offset(mw_code(tile[x]));
-          const int z = y + code_offset(mw_code(tile[y]));
-          if ((tile[z] >> 10) >= MW_V0) lab = ((z / CL_TP + tile_t0) << 8) | (z % CL_TP - 2);
+        if (mw_core<W>(c)) {
+          const int x = (int)c;
+          const int y = x + mw_offset(tile[x] & 15);
+          const int z = y + mw_offset(tile[y] & 15);
+          if ((tile[z] & 15u) == MW_SELF && tile[z] >= qmin16)
+            lab = ((z / CL_TP + tile_t0) << 8) | (z % CL_TP - 2);
         }
         sample_label[s] = lab;
       }
-      __syncthreads();
+      loads_done();
     }
-    // the clear writes only cells that no wave reads any more
-    scatter_mw<ROWS, PRE, NT>(tile, in, R, cur, tile_t0, np, false);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PRE; ++j)
+      if (h.first + j * 64 < h.end) tile[cell[j]] = 0;
+    if (dense) {
+      for (uint32_t s0 = h.first + PRE * 64; s0 < h.end; s0 += 64) tile[load_cell(s0, nullptr)] = 0;
+      loads_done();
+    }
     __syncthreads();
     R = Rn;
-    cur = nxt;
+    h = hn;
   }
 }
 

@@ -449,11 +449,22 @@ void launch_cluster(tpc_ctx* c, const ZsArgs& za, uint32_t nblk_s, uint32_t n_ur
   {
     StageTimer tm(c, 1);
     if (c->tune.cl_mode == 2) {
-      // windows shared by two waves (W >= 24, checked by tpc_set_tuning)
-      if constexpr (W >= 24)
-        k_cluster_peaks_mw<W, K, 2, 2><<<ngrid, 128, 0, s>>>(za, c->zblk, nblk_s, nwin, nchunk,
-                                                             n_ur, c->win, c->crec,
-                                                             co.sample_label, c->d_par, c->d_st);
+      // windows shared by two waves (W >= 24, checked by tpc_set_tuning).  The
+      // waves prefetch 3 steps of 64 samples each, or 4 where a window and its
+      // halo average more than 256 samples, so that some rows exceed 3 steps
+      // and would load the rest late: a 2 ms slice (166 per window) takes 1.60
+      // ms with 3 and 1.65 with 4, a precision-stress chunk (480 per window)
+      // 0.69 and 0.60 ms
+      if constexpr (W >= 24) {
+        auto launch = [&](auto pre) {
+          k_cluster_peaks_mw<W, K, 2, decltype(pre)::value><<<ngrid, 128, 0, s>>>(
+              za, c->zblk, nblk_s, nwin, nchunk, n_ur, c->win, c->crec, co.sample_label, c->d_par,
+              c->d_st);
+        };
+        const double mean = (double)za.n_samples / nwt * (W + 2 * CL_HALO) / W;
+        if (mean > 256) launch(std::integral_constant<int, 4>{});
+        else launch(std::integral_constant<int, 3>{});
+      }
     } else {
       if (c->tune.cl_mode == 1) {
         // streaming pass, then the windowed pass over the chunks it handed back
