@@ -34,12 +34,38 @@ __global__ __launch_bounds__(256) void k_qc_fill(const uint16_t* __restrict__ qt
   const uint32_t n_trk = ok ? scan_count(n_trk_dev, trk_cap) : 0u;
   const uint32_t stride = gridDim.x * blockDim.x;
   uint32_t on = 0, off = 0;
-  for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < n_cl; c += stride) {
-    atomicAdd(&h[w][QC_QTOT + min((uint32_t)qtot[c] >> 3, 255u)], 1u);
-    atomicAdd(&h[w][QC_QMAX + min((uint32_t)qmax[c] >> 2, 255u)], 1u);
-    if (cluster_track[c] >= 0) ++on;
+  auto count = [&](uint32_t qt, uint32_t qm, int32_t ct) {
+    atomicAdd(&h[w][QC_QTOT + min(qt >> 3, 255u)], 1u);
+    atomicAdd(&h[w][QC_QMAX + min(qm >> 2, 255u)], 1u);
+    if (ct >= 0) ++on;
     else ++off;
+  };
+  // eight clusters per thread and step in four 16-byte loads, where the arrays
+  // allow them (the caller may pass views).  Bound by the bytes in flight: on
+  // 1.7e7 clusters (1.4e8 bytes) from HBM the call took 99 us with a cluster per
+  // thread and step, 41 us with eight (512 or 2048 workgroups: 40 and 44)
+  uint32_t done = 0;
+  if ((((uintptr_t)qtot | (uintptr_t)qmax | (uintptr_t)cluster_track) & 15) == 0) {
+    const uint4* qt8 = reinterpret_cast<const uint4*>(qtot);
+    const uint4* qm8 = reinterpret_cast<const uint4*>(qmax);
+    const int4* ct4 = reinterpret_cast<const int4*>(cluster_track);
+    const uint32_t n8 = n_cl / 8;
+    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < n8; g += stride) {
+      const uint4 a = qt8[g], b = qm8[g];
+      const int4 c0 = ct4[2 * (size_t)g], c1 = ct4[2 * (size_t)g + 1];
+      count(a.x & 0xFFFFu, b.x & 0xFFFFu, c0.x);
+      count(a.x >> 16, b.x >> 16, c0.y);
+      count(a.y & 0xFFFFu, b.y & 0xFFFFu, c0.z);
+      count(a.y >> 16, b.y >> 16, c0.w);
+      count(a.z & 0xFFFFu, b.z & 0xFFFFu, c1.x);
+      count(a.z >> 16, b.z >> 16, c1.y);
+      count(a.w & 0xFFFFu, b.w & 0xFFFFu, c1.z);
+      count(a.w >> 16, b.w >> 16, c1.w);
+    }
+    done = n8 * 8;
   }
+  for (uint32_t c = done + blockIdx.x * blockDim.x + threadIdx.x; c < n_cl; c += stride)
+    count(qtot[c], qmax[c], cluster_track[c]);
   for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n_trk; j += stride) {
     const uint32_t n = hit_start[j + 1] - hit_start[j];
     atomicAdd(&h[w][QC_NHITS + min(n, (uint32_t)NROW)], 1u);

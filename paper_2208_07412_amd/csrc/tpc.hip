@@ -1146,10 +1146,13 @@ int tpc_qc_histograms(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, 
   if (!c || !cl || !tr || !hist || !cl->n_clusters || !cl->qtot || !cl->qmax || !tr->n_tracks ||
       !tr->hit_start || !tr->cluster_track)
     return TPC_ERR_ARG;
-  k_qc_fill<<<QC_WG, 256, 0, c->stream>>>(cl->qtot, cl->qmax, tr->cluster_track, cl->n_clusters,
-                                          cl->capacity, tr->hit_start, tr->n_tracks,
-                                          tr->capacity, c->qc_part, c->d_st);
-  k_qc_sum<<<QC_BINS, 256, 0, c->stream>>>(c->qc_part, QC_WG, hist);
+  // as many workgroups as eight entries per thread fill, up to QC_WG
+  const uint32_t nwg =
+      grid_for(cl->capacity > tr->capacity ? cl->capacity : tr->capacity, 8 * 256, QC_WG);
+  k_qc_fill<<<nwg, 256, 0, c->stream>>>(cl->qtot, cl->qmax, tr->cluster_track, cl->n_clusters,
+                                        cl->capacity, tr->hit_start, tr->n_tracks, tr->capacity,
+                                        c->qc_part, c->d_st);
+  k_qc_sum<<<QC_BINS, 256, 0, c->stream>>>(c->qc_part, nwg, hist);
   return launch_ok();
 }
 
