@@ -130,13 +130,35 @@ __device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_read
 // ------------------------------------------------------------ wave64 scans
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
+// A value moved between lanes by the DPP control CTRL, 0 where no lane is
+// named (or the row of 16 is not in the mask ROWS).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_0(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_add(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return v + (T)dpp_or_0<CTRL, ROWS>((uint32_t)v);
+  } else {
+    const uint64_t u = (uint64_t)v;
+    const uint64_t o = (uint64_t)dpp_or_0<CTRL, ROWS>((uint32_t)u) |
+                       ((uint64_t)dpp_or_0<CTRL, ROWS>((uint32_t)(u >> 32)) << 32);
+    return v + (T)o;
+  }
+}
+// Inclusive scan over the 64 lanes of a wave, all of them active: shifts
+// within rows of 16, then each row's last value to the rows after it (lane
+// moves in the vector unit instead of LDS permutations).
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const T o = __shfl_up(v, d, 64);
-    if ((int)lane_id() >= d) v += o;
-  }
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "32- and 64-bit integers");
+  v = dpp_add<0x111, 0xF>(v);
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);
+  v = dpp_add<0x143, 0xC>(v);
   return v;
 }
 

@@ -987,11 +987,12 @@ int tpc_compress(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, tpc_c
                     tr->n_tracks, tr->capacity, tr->hit_capacity};
   const int64_t b30 = cm_b30(c);
   if (out->res_hist) k_fill<uint32_t><<<1, 256, 0, s>>>(out->res_hist, 0u, 256);
-  // the hits' residual codes, cached between the two track passes
+  // the hits' codes and the tracks' units, kept between the two track passes
+  // (the units in scratch that only the track fit uses, one entry per tracklet)
   const uint32_t res_cap = (uint32_t)c->max.max_clusters;
   k_cm_track_bits<<<grid_for(tr->capacity, 4, kCapStream), 256, 0, s>>>(
-      cv, tv, b30, c->d_par, c->cm_a, out->res_hist, c->cm_res, res_cap, c->d_st);
-  k_cm_row_bits<<<grid_for(n_ur, 4, 4096), 256, 0, s>>>(cv, tr->cluster_track, c->cm_b, c->d_st);
+      cv, tv, b30, c->d_par, c->cm_a, c->f_range, out->res_hist, c->cm_res, res_cap, c->d_st);
+  k_cm_row_bits<<<n_ur, 256, 0, s>>>(cv, tr->cluster_track, c->cm_b, c->d_st);
   run_scan<unsigned long long>(c, CmGetU32{c->cm_a}, CmEmitTrack{out->stream, out->capacity},
                                tr->n_tracks, tr->capacity, c->cm_tot, (uint32_t*)nullptr);
   run_scan<unsigned long long>(
@@ -1003,8 +1004,8 @@ int tpc_compress(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, tpc_c
                               out->n_words, c->cm_info, c->d_st);
   k_cm_clear<<<grid_for(out->capacity, 256, 2048), 256, 0, s>>>(out->stream, c->cm_info, c->d_st);
   k_cm_track_write<<<grid_for(tr->capacity, 4, kCapStream), 256, 0, s>>>(
-      cv, tv, b30, c->d_par, out->stream, c->cm_info, c->cm_res, res_cap, c->d_st);
-  k_cm_row_write<<<grid_for(n_ur, 4, 4096), 256, 0, s>>>(cv, tr->cluster_track, out->stream,
+      cv, tv, b30, c->d_par, c->f_range, out->stream, c->cm_info, c->cm_res, res_cap, c->d_st);
+  k_cm_row_write<<<n_ur, 256, 0, s>>>(cv, tr->cluster_track, out->stream,
                                                          tr->n_tracks, tr->capacity, c->cm_info,
                                                          c->d_st);
   return launch_ok();
@@ -1026,6 +1027,21 @@ int tpc_decompress(tpc_ctx* c, const uint32_t* stream, uint32_t stream_words,
                                c->cm_tot, (uint32_t*)nullptr);
   const CmDecOut o{out->capacity, out->unit, out->row, out->y_fx, out->z_fx,
                    out->qtot, out->qmax, out->flags, out->track};
+  // In two steps where the scratch holds a raw record per cluster that the
+  // outputs take (16 bytes per cluster of the context's bound), else in one.
+  if (out->capacity <= c->max.max_clusters) {
+    CmRaw* raw = reinterpret_cast<CmRaw*>(c->cm_res);
+    uint32_t* fields = reinterpret_cast<uint32_t*>(c->f_state);  // six words per tracklet
+    k_cm_parse_tracks<<<grid_for(c->max.max_tracklets, 64, 16384), 64, 0, s>>>(
+        stream, c->cm_info, c->cm_b, out->capacity, raw, fields, c->d_st);
+    k_cm_parse_rows<<<grid_for((uint64_t)c->max.max_units * NROW, 4, 4096), 256, 0, s>>>(
+        stream, c->cm_info, c->cm_b, c->cm_tot, out->capacity, raw, c->d_st);
+    k_cm_dec_model<<<grid_for(c->max.max_tracklets, 4, kCapStream), 256, 0, s>>>(
+        c->cm_info, c->cm_b, c->cm_a, raw, fields, cm_b30(c), c->d_par, o, c->d_st);
+    k_cm_dec_rest<<<grid_for(out->capacity, 256, 4096), 256, 0, s>>>(c->cm_info, c->cm_b, raw, o,
+                                                                     c->d_st);
+    return launch_ok();
+  }
   k_cm_dec_tracks<<<grid_for(c->max.max_tracklets, 256, 4096), 256, 0, s>>>(
       stream, c->cm_info, c->cm_b, cm_b30(c), c->d_par, o, c->d_st);
   k_cm_dec_rows<<<grid_for((uint64_t)c->max.max_units * NROW, 4, 4096), 256, 0, s>>>(
