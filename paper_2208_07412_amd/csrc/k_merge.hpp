@@ -4,15 +4,14 @@
 // A segment's two ends (innermost and outermost hit) carry their global
 // position, drift z and the tangent of the segment's outward fit there.  Ends
 // are binned by (frame, side, 30.5 cm squares of the bending plane, 36 cm of
-// drift); one lane per end tests the ends of later segments in the 3 x 3 x 3
-// cells around it with the joining rule (every joinable pair has ends within
-// 35 cm in drift and 30 cm in the bending plane, so the cells hold all
-// candidates), and joins
-// segments by a lock-free union-find that always hangs the larger root under
+// drift); one lane per end finds the ends close to it in the 3 x 3 x 3 cells
+// around it (every joinable pair has ends within 35 cm in drift and 30 cm in the
+// bending plane, so the cells hold all candidates); the pairs go through the
+// joining rule, and join segments by a lock-free union-find that always hangs the larger root under
 // the smaller, so the final root of a component is its smallest segment
 // whatever the order of the unions.  The members of each component are then
-// sorted by (root, index), and one lane per component fits all its hits in
-// FP64 in ascending segment order: the algebraic circle fit about the
+// sorted by (root, index), and 8 or 16 lanes per component fit all its hits in
+// FP64, added up in ascending segment order: the algebraic circle fit about the
 // centroid, the line of drift z against the unwrapped azimuth, the beam-axis
 // crossing and T0.  The arithmetic follows the joining rule and the fit as
 // stated in include/tpc.h.
@@ -207,41 +206,108 @@ __device__ __forceinline__ bool mg_follows(double C, double tgl, const double* a
   return ok;
 }
 
-// The drift z and bending-plane position of every end, in cell order, so
-// that the candidate scans below read consecutive memory.
+// What the pair search needs of an end, in cell order: position (drift z in
+// 2^-16 cm, exact) with 2 * segment + end, and the tangent, curvature and dip.
+struct MgPos {
+  float x, y;
+  int32_t z;
+  uint32_t id;
+};
+struct MgDir {
+  float tx, ty, C, tgl;
+};
 __global__ void k_mg_pack(const uint32_t* __restrict__ cell_ends, const uint32_t* total_dev,
-                          const double* __restrict__ e_all, double* __restrict__ pk,
+                          MgSegs S, MgPos* __restrict__ pos, MgDir* __restrict__ dir,
                           const DevStatus* st) {
   if (failed(st)) return;
   const uint32_t total = *total_dev;
   for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < total; k += gridDim.x * blockDim.x) {
-    const uint32_t e = cell_ends[k];
-    const double* E = e_all + (size_t)(e >> 1) * 10 + 5 * (e & 1);
-    pk[3 * (size_t)k] = E[2];
-    pk[3 * (size_t)k + 1] = E[0];
-    pk[3 * (size_t)k + 2] = E[1];
+    const uint32_t e = cell_ends[k], j = e >> 1;
+    const double* E = S.e + (size_t)j * 10 + 5 * (e & 1);
+    pos[k] = MgPos{(float)E[0], (float)E[1], (int32_t)(E[2] * 65536.0), e};
+    dir[k] = MgDir{(float)E[3], (float)E[4], (float)S.C[j], (float)S.tgl[j]};
   }
 }
 
-// The joining test of end t (cell order) against candidate end k: the
-// remaining gates and cuts, then the union; near ties flag both segments.
-__device__ __forceinline__ void mg_pair_check(const MgSegs& S, const uint32_t* cell_ends,
-                                              const double* pk, uint32_t t, uint32_t k,
+// A cut in FP32: clearly missed, or within a part in a thousand (a NaN counts
+// as within).  The FP32 errors stay below a third of that: positions are good to
+// 8e-6 cm, so distances off a circle to 1e-4 cm where the cut's margin is 5e-4.
+__device__ __forceinline__ void mg_cut32(float v, float cut, bool& missed, bool& close) {
+  missed |= v > cut * 1.001f;
+  close |= !(v < cut * 0.999f || v > cut * 1.001f);
+}
+
+// mg_follows in FP32: with s and p the components of the step across and along
+// the tangent and q = |centre to b| / |r|, the distance off the circle is
+// |2 s + C d^2| / (1 + q), the arc 2 atan(u) / C with u = C p / (q + 1 + C s) and
+// the tangent there (tx - C dy, ty + C dx) / q, none of which cancels for stiff
+// tracks.  atan(u) / u is an interpolation in u^2 at Chebyshev points of [0, 1]
+// (relative error 1e-6).
+__device__ __forceinline__ void mg_follows32(const MgDir& a, const MgDir& b, float dx, float dy,
+                                             float dz, bool& missed, bool& close) {
+  const float aC = fabsf(a.C);
+  const float C = aC >= (float)MG_C_LINE ? a.C : 0.0f;
+  const float s = a.ty * dx - a.tx * dy, p = a.tx * dx + a.ty * dy;
+  const float c1 = 1.0f + C * s, c2 = C * p;
+  const float q = __builtin_amdgcn_sqrtf(c1 * c1 + c2 * c2);
+  const float perp = fabsf(2.0f * s + C * (s * s + p * p)) * __builtin_amdgcn_rcpf(1.0f + q);
+  const float iqc = __builtin_amdgcn_rcpf(q + c1), u = c2 * iqc, t = u * u;
+  float k = 0.00764835393f;
+  k = k * t - 0.0363604315f;
+  k = k * t + 0.0831264555f;
+  k = k * t - 0.134478644f;
+  k = k * t + 0.198720396f;
+  k = k * t - 0.333256781f;
+  k = k * t + 0.999999225f;
+  const float arc = 2.0f * p * iqc * k, len = fabsf(arc);
+  // either form, towards the centre or around the circle, beyond the error bounds
+  close |= fabsf(aC - (float)MG_C_LINE) < 1e-8f || !(c1 > 0.1f) || !(aC < 1.0f) ||
+           !(fabsf(a.tgl) < 8.0f);
+  mg_cut32(perp, (float)MG_PERP, missed, close);
+  mg_cut32(len, (float)MG_GAP, missed, close);
+  mg_cut32(fabsf(dz - a.tgl * arc), (float)MG_DZ + (float)MG_DZ_ARC * len, missed, close);
+  mg_cut32(fabsf((a.tx - C * dy) * b.ty - (a.ty + C * dx) * b.tx), (float)MG_SIN * q, missed,
+           close);
+}
+
+// Whether a pair has to go through the FP64 test: not if a cut is clearly missed
+// and none is so close that FP64 could call it a near tie.
+__device__ __forceinline__ bool mg_maybe(const MgPos& pa, const MgPos& pb, const MgDir& a,
+                                         const MgDir& b) {
+  const float dx = pb.x - pa.x, dy = pb.y - pa.y, dz = (float)(pb.z - pa.z) * (1.0f / 65536.0f);
+  bool missed = false, close = false;
+  mg_cut32(__builtin_amdgcn_sqrtf(dx * dx + dy * dy), (float)MG_GAP, missed, close);
+  const float ca = fabsf(a.C), cb = fabsf(b.C);
+  mg_cut32(fabsf(ca - cb), (float)MG_DC_REL * fmaxf(ca, cb) + (float)MG_DC_ABS, missed, close);
+  mg_follows32(a, b, dx, dy, dz, missed, close);
+  mg_follows32(b, a, -dx, -dy, -dz, missed, close);
+  return close || !missed;
+}
+
+// The joining test of ends e and f in FP64 (the same either way round): the
+// gates and cuts, then the union; near ties flag both segments.
+__device__ __forceinline__ void mg_pair_check(const MgSegs& S, uint32_t e, uint32_t f,
                                               uint32_t* parent, uint8_t* near_tie) {
-  const uint32_t e = cell_ends[t], f = cell_ends[k];
   const uint32_t A = e >> 1, B = f >> 1;
   const double* a = S.e + (size_t)A * 10 + 5 * (e & 1);
   const double* b = S.e + (size_t)B * 10 + 5 * (f & 1);
-  const double ax = pk[3 * (size_t)t + 1], ay = pk[3 * (size_t)t + 2];
-  const double bx = pk[3 * (size_t)k + 1], by = pk[3 * (size_t)k + 2];
-  const double dxy = sqrt((ax - bx) * (ax - bx) + (ay - by) * (ay - by));
-  const double CA = S.C[A], CB = S.C[B], ca = fabs(CA), cb = fabs(CB), cm = ca > cb ? ca : cb;
+  const double ax = a[0], ay = a[1], bx = b[0], by = b[1];
+  const double d2 = (ax - bx) * (ax - bx) + (ay - by) * (ay - by);
+  // beyond the near-tie band of the gap cut nothing can pass or tie (squared
+  // distances: the band's margin of 2e-9 dwarfs the rounding)
+  constexpr double g = MG_GAP * (1 + 2 * MG_TIE);
+  if (!(fabs(a[2] - b[2]) <= MG_DZMAX) || !(d2 <= g * g)) return;
+  const double dxy = sqrt(d2);
+  const double ca = fabs(S.C[A]), cb = fabs(S.C[B]), cm = ca > cb ? ca : cb;
   bool tie = false;
   bool ok = mg_cut(dxy, MG_GAP, tie);
   if (ok) {
     ok = mg_cut(fabs(ca - cb), MG_DC_REL * cm + MG_DC_ABS, tie);
-    ok &= mg_follows(CA, S.tgl[A], a, b, tie);
-    ok &= mg_follows(CB, S.tgl[B], b, a, tie);
+#pragma unroll 1
+    for (int way = 0; way < 2; ++way) {  // b seen from a, a seen from b
+      const uint32_t J = way ? B : A;
+      ok &= mg_follows(S.C[J], S.tgl[J], way ? b : a, way ? a : b, tie);
+    }
   }
   if (tie) {
     near_tie[A] = 1;
@@ -251,125 +317,143 @@ __device__ __forceinline__ void mg_pair_check(const MgSegs& S, const uint32_t* c
 }
 
 // One lane per end, ends taken in cell order (the lanes of a wave mostly
-// share their cells and so scan the same neighbour cells in step): the ends of
-// later segments in the 3 x 3 x 3 cells around it (nine runs of three
-// consecutive drift cells) are gated on the packed drift z and position; the
-// pairs that pass go to the wave's queue in LDS, and every
-// 64 of them are tested by the 64 lanes together (the full test is long and
-// few lanes pass a gate at a time).
-#define MG_QCAP 128
-__global__ __launch_bounds__(256) void k_mg_pairs(MgSegs S, uint32_t nzb,
-                                                  const uint32_t* total_dev,
-                                                  const uint32_t* __restrict__ cell_off,
-                                                  const uint32_t* __restrict__ cell_ends,
-                                                  const uint32_t* __restrict__ cell_of_end,
-                                                  const double* __restrict__ pk,
-                                                  uint32_t* __restrict__ parent,
-                                                  uint8_t* __restrict__ near_tie,
-                                                  const DevStatus* st) {
-  __shared__ uint32_t qa[4][MG_QCAP], qb[4][MG_QCAP];
+// share their cells and so scan the same neighbour cells in step).  Of the
+// 3 x 3 x 3 cells around an end half are scanned, so that a pair is met once:
+// the rest of its own cell and the cell above in drift, and four neighbouring
+// columns of three drift cells, each a run of consecutive ends.  A wave takes
+// 64 ends and one of the five runs at a time (a grid of a few waves per SIMD
+// strides over these), four candidates loaded together and the next four on
+// their way.  Pairs that pass the gates on drift z and distance go to a queue of
+// the wave in LDS, and every 64 of them are tested in FP32 by the 64 lanes
+// together; the few that FP32 cannot rule out go to a second queue for the FP64
+// test (two helix extrapolations with an arc tangent each), 64 at a time again.
+// On a chunk of 37 collisions (139,000 segments) 342 us; 1364 with one wave per 64
+// ends for all 27 cells, every gated pair tested in FP64, a candidate at a time.
+#define MG_SCAN 4
+#define MG_RUNS 5
+#define MG_QCAP (64 + 64 * MG_SCAN)
+#define MG_PAIR_BLOCKS 1024  // four per CU: the registers hold four waves per SIMD
+__global__ __launch_bounds__(256, 4) void k_mg_pairs(
+    MgSegs S, uint32_t nzb, const uint32_t* total_dev, const uint32_t* __restrict__ cell_off,
+    const uint32_t* __restrict__ cell_of_end, const MgPos* __restrict__ pos,
+    const MgDir* __restrict__ dir, uint32_t* __restrict__ parent, uint8_t* __restrict__ near_tie,
+    const DevStatus* st) {
+  __shared__ uint32_t qa[4][MG_QCAP], qb[4][MG_QCAP];  // gated pairs: places in cell order
+  __shared__ uint32_t ra[4][128], rb[4][128];          // pairs for FP64: ends
   if (failed(st)) return;
   const uint32_t total = *total_dev;
   const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint64_t below = (1ull << lane) - 1ull;
-  for (uint32_t t0 = blockIdx.x * blockDim.x + w * 64; t0 < total;
-       t0 += gridDim.x * blockDim.x) {  // uniform per wave
-    const uint32_t t = t0 + lane;
-    const bool have = t < total;
-    uint32_t A = 0, zb = 0, ix = 0, iy = 0, fs = 0;
-    double az = 0, ax = 0, ay = 0;
-    if (have) {
-      const uint32_t e = cell_ends[t];
-      A = e >> 1;
-      const uint32_t cell = cell_of_end[e];
-      zb = cell % nzb;
-      ix = (cell / nzb) % MG_NXY;
-      iy = (cell / nzb / MG_NXY) % MG_NXY;
-      fs = cell / nzb / MG_NXY / MG_NXY;
-      az = pk[3 * (size_t)t];
-      ax = pk[3 * (size_t)t + 1];
-      ay = pk[3 * (size_t)t + 2];
+  auto in_order = [] {  // a wave's LDS writes before its reads, and the reverse
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  uint32_t qn = 0, rn = 0;  // queued pairs (the same in every lane)
+  const uint32_t items = (total + 63) / 64 * MG_RUNS;
+  // one step past the items empties the queues
+  const uint32_t nw = gridDim.x * 4;
+  for (uint32_t item = blockIdx.x * 4 + w;; item += nw) {  // uniform per wave
+    const bool last = item >= items;
+    const uint32_t run = item % MG_RUNS, t = item / MG_RUNS * 64 + lane;
+    MgPos me{0, 0, 0, 0};
+    uint32_t k0 = 0, len = 0;
+    if (!last && t < total) {
+      me = pos[t];
+      const uint32_t cell = cell_of_end[me.id];
+      const uint32_t zb = cell % nzb, ix = (cell / nzb) % MG_NXY, iy = (cell / nzb / MG_NXY) % MG_NXY;
+      const uint32_t up = zb + 1 < nzb ? 1 : 0, dn = zb > 0 ? 1 : 0;
+      if (run == 0) {
+        k0 = t + 1;
+        len = cell_off[cell + up + 1] - k0;
+      } else {
+        // runs 1 to 4: (dx, dy) = (1, 0), (-1, 1), (0, 1), (1, 1)
+        const int x2 = (int)ix + (run == 1 ? 1 : (int)run - 3), y2 = (int)iy + (run > 1);
+        if (x2 >= 0 && x2 < MG_NXY && y2 < MG_NXY) {
+          const uint32_t cb = cell + (uint32_t)((run > 1 ? MG_NXY : 0) + x2 - (int)ix) * nzb;
+          k0 = cell_off[cb - dn];
+          len = cell_off[cb + up + 1] - k0;
+        }
+      }
     }
-    uint32_t qn = 0;  // queued pairs (the same in every lane)
-    for (int ci = 0; ci < 9; ++ci) {
-      const int dy = ci / 3 - 1, dx = ci % 3 - 1;
-      uint32_t k0 = 0, k1 = 0;
-      const int x2 = (int)ix + dx, y2 = (int)iy + dy;
-      if (have && x2 >= 0 && x2 < MG_NXY && y2 >= 0 && y2 < MG_NXY) {
-        // the drift cells zb - 1, zb, zb + 1 (those that exist) of a
-        // neighbouring (x, y) cell are consecutive cells: their ends form one
-        // run, taken in the same order as cell by cell
-        const uint32_t cb = ((fs * MG_NXY + (uint32_t)y2) * MG_NXY + (uint32_t)x2) * nzb;
-        const uint32_t zlo = zb > 0 ? zb - 1 : 0, zhi = zb + 1 < nzb ? zb + 1 : nzb - 1;
-        k0 = cell_off[cb + zlo];
-        k1 = cell_off[cb + zhi + 1];
-      }
-      const uint32_t len = k1 - k0;
-      const uint32_t maxlen = (uint32_t)wave_max_i32((int32_t)len);
-      // each candidate's gate data is loaded one candidate ahead of its test
-      double bz_next = 0.0, bx_next = 0.0, by_next = 0.0;
-      if (len > 0) {
-        bz_next = pk[3 * (size_t)k0];
-        bx_next = pk[3 * (size_t)k0 + 1];
-        by_next = pk[3 * (size_t)k0 + 2];
-      }
-      for (uint32_t it = 0; it < maxlen; ++it) {
-        bool pass = false;
-        const uint32_t k = k0 + it;
-        const double bz = bz_next, bx = bx_next, by = by_next;
-        if (it + 1 < len) {
-          bz_next = pk[3 * (size_t)(k + 1)];
-          bx_next = pk[3 * (size_t)(k + 1) + 1];
-          by_next = pk[3 * (size_t)(k + 1) + 2];
-        }
-        if (it < len) {
-          if (fabs(az - bz) <= MG_DZMAX) {
-            const double d2 = (ax - bx) * (ax - bx) + (ay - by) * (ay - by);
-            // beyond the near-tie band of the gap cut nothing can pass or tie
-            // (squared distances: the band's margin of 2e-9 dwarfs the rounding)
-            constexpr double g = MG_GAP * (1 + 2 * MG_TIE);
-            pass = d2 <= g * g && (cell_ends[k] >> 1) > A;
-          }
-        }
-        const uint64_t m = __ballot(pass);
-        if (m) {  // uniform
-          const uint32_t pos = qn + (uint32_t)__popcll(m & below);
+    const uint32_t maxlen = (uint32_t)wave_max_i32((int32_t)len);
+    const uint32_t full = last ? 1 : 64;  // pairs that are tested together
+    // a round's candidates (an end that exists, in every lane)
+    auto load = [&](uint32_t it, MgPos (&c)[MG_SCAN]) {
+#pragma unroll
+      for (uint32_t i = 0; i < MG_SCAN; ++i) c[i] = pos[min(k0 + it + i, total - 1)];
+    };
+    MgPos cur[MG_SCAN], nxt[MG_SCAN];
+    if (maxlen) load(0, cur);
+    uint32_t it = 0;
+    do {
+      if (maxlen) {
+        load(it + MG_SCAN, nxt);
+#pragma unroll
+        for (uint32_t i = 0; i < MG_SCAN; ++i) {
+          const float ex = me.x - cur[i].x, ey = me.y - cur[i].y;
+          const int32_t ez = me.z - cur[i].z;
+          // drift exactly; distance with a margin above the FP32 positions' errors
+          constexpr float g = (float)MG_GAP + 1e-3f;
+          constexpr int32_t gz = (int32_t)(MG_DZMAX * 65536);
+          const bool pass = it + i < len && ez <= gz && ez >= -gz && ex * ex + ey * ey <= g * g &&
+                            (cur[i].id ^ me.id) > 1;  // not the segment's own ends
+          const uint64_t m = __ballot(pass);
+          const uint32_t at = qn + (uint32_t)__popcll(m & below);
           if (pass) {
-            qa[w][pos] = t;
-            qb[w][pos] = k;
+            qa[w][at] = t;
+            qb[w][at] = k0 + it + i;
           }
           qn += (uint32_t)__popcll(m);
-          if (qn >= 64) {  // uniform: the 64 newest pairs, one per lane
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t q = qn - 64 + lane;
-            mg_pair_check(S, cell_ends, pk, qa[w][q], qb[w][q], parent, near_tie);
-            qn -= 64;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-          }
+          cur[i] = nxt[i];
         }
       }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (lane < qn) mg_pair_check(S, cell_ends, pk, qa[w][lane], qb[w][lane], parent, near_tie);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+      while (qn >= full) {  // uniform: the newest pairs, one per lane
+        in_order();
+        const uint32_t m = min(qn, 64u);
+        bool go = false;
+        uint32_t e = 0, f = 0;
+        if (lane < m) {
+          const uint32_t a = qa[w][qn - m + lane], b = qb[w][qn - m + lane];
+          const MgPos pa = pos[a], pb = pos[b];
+          go = mg_maybe(pa, pb, dir[a], dir[b]);
+          e = pa.id;
+          f = pb.id;
+        }
+        qn -= m;
+        const uint64_t mask = __ballot(go);
+        const uint32_t at = rn + (uint32_t)__popcll(mask & below);
+        if (go) {
+          ra[w][at] = e;
+          rb[w][at] = f;
+        }
+        rn += (uint32_t)__popcll(mask);
+        in_order();
+        if (rn >= 64) {  // uniform
+          mg_pair_check(S, ra[w][rn - 64 + lane], rb[w][rn - 64 + lane], parent, near_tie);
+          rn -= 64;
+          in_order();
+        }
+      }
+      it += MG_SCAN;
+    } while (it < maxlen);
+    if (last) break;
   }
+  if (lane < rn) mg_pair_check(S, ra[w][lane], rb[w][lane], parent, near_tie);
 }
 
-// Global position of every hit of every track (the fit reads it three times):
+// Global position and drift of every hit of every track (the fit reads the position three times):
 // one thread per hit, its cluster's (unit,row) found by a binary search of the
 // row starts (one lane per track walking its hits took 0.68 ms on a 2 ms
 // Pb-Pb slice, the longest tracks setting the pace; per hit: 0.21 ms).
 __global__ void k_mg_hits(const uint32_t* __restrict__ crow, uint32_t n_ur,
-                          const int32_t* __restrict__ y_fx, const uint32_t* n_cl_dev,
-                          uint32_t cl_cap, const uint32_t* __restrict__ hit_start,
+                          const int32_t* __restrict__ y_fx, const int32_t* __restrict__ z_fx,
+                          const uint32_t* n_cl_dev, uint32_t cl_cap,
+                          const uint32_t* __restrict__ hit_start,
                           const uint32_t* __restrict__ hits, uint32_t hit_cap,
                           const uint32_t* n_trk_dev, uint32_t trk_cap,
                           const double* __restrict__ cs18, double* __restrict__ hxy,
-                          const DevParams* __restrict__ P, const DevStatus* st) {
+                          int32_t* __restrict__ hz, const DevParams* __restrict__ P,
+                          const DevStatus* st) {
   if (failed(st)) return;
   const uint32_t n = scan_count(n_trk_dev, trk_cap);
   const uint32_t n_cl = scan_count(n_cl_dev, cl_cap);
@@ -383,6 +467,7 @@ __global__ void k_mg_hits(const uint32_t* __restrict__ crow, uint32_t n_ur,
     const double x = P->xd[ur % NROW], y = y_fx[c] / 65536.0;
     hxy[2 * (size_t)h] = x * ca - y * sa;
     hxy[2 * (size_t)h + 1] = x * sa + y * ca;
+    hz[h] = z_fx[c];
   }
 }
 
@@ -413,121 +498,173 @@ __global__ void k_mg_labels(const uint32_t* __restrict__ parent, const uint32_t*
   }
 }
 
-// One lane per component (the first of its run in the sorted members): the
-// FP64 helix fit of all its hits, members in ascending index.
-__global__ __launch_bounds__(64) void k_mg_fit(const uint32_t* __restrict__ skey,
-                                               const uint32_t* __restrict__ sidx,
-                                               const uint32_t* n_trk_dev, uint32_t trk_cap,
-                                               const int32_t* __restrict__ z_fx,
-                                               const uint32_t* __restrict__ hit_start,
-                                               const uint32_t* __restrict__ hits,
-                                               uint32_t hit_cap, const double* __restrict__ hxy,
-                                               double* __restrict__ fit, const DevStatus* st) {
-  if (failed(st)) return;
-  const uint32_t n = scan_count(n_trk_dev, trk_cap);
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+// The lanes' values of one array, in the lanes' order.
+template <int G>
+__device__ __forceinline__ void mg_row(const double* lds, double (&x)[G]) {
+  const double2* v = reinterpret_cast<const double2*>(lds);
+#pragma unroll
+  for (int i = 0; i < G / 2; ++i) {
+    const double2 t = v[i];
+    x[2 * i] = t.x;
+    x[2 * i + 1] = t.y;
+  }
+}
+
+// G lanes per component (the first of its run in the sorted members): the FP64
+// helix fit of all its hits, members in ascending index.  The lanes take a
+// member's hits G at a time and compute their terms (the arc tangent of the
+// azimuth above all) together; the sums and the unwrapped azimuth are still
+// added hit by hit in their order, each lane adding up one sum from the terms
+// that the lanes leave in LDS, so the results are those of one lane.  (A term of
+// +0 stands for the lanes past a member's last hit: it changes no sum, none of
+// which can be -0.)  lds: [64 / G][6][G + 2] doubles (padded: 16-byte reads
+// spread over the banks).
+template <int G>
+__device__ __forceinline__ void mg_fit_rows(const uint32_t* __restrict__ skey,
+                                            const uint32_t* __restrict__ sidx, uint32_t n,
+                                            const uint32_t* __restrict__ hit_start,
+                                            uint32_t hit_cap, const double* __restrict__ hxy,
+                                            const int32_t* __restrict__ hz,
+                                            double* __restrict__ fit, double* rows) {
+  const uint32_t g = threadIdx.x / G, q = threadIdx.x % G;
+  double(*lds)[G + 2] = reinterpret_cast<double(*)[G + 2]>(rows) + 6 * g;
+  lds[5][q] = 1.0;
+  auto in_order = [] {  // a wave's LDS writes before its reads, and the reverse
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto of_lane = [](double v, int k) { return __shfl(v, k, G); };
+  const double2* xy = reinterpret_cast<const double2*>(hxy);  // by k_mg_hits
+  // the arrays whose products are this lane's sum in the second pass, of
+  // u, v, uu, vv, uv: uu, vv, uv, uuu, vvv, uvv, vuu
+  const uint32_t fa = 0x4432010u >> 4 * (q & 7) & 7, fb = 0x0110110u >> 4 * (q & 7) & 7;
+  for (uint32_t i = blockIdx.x * (64 / G) + g; i < n; i += gridDim.x * (64 / G)) {
     const uint32_t root = skey[i];
     if (i > 0 && skey[i - 1] == root) continue;
     uint32_t end = i + 1;
     while (end < n && skey[end] == root) ++end;
     double* f = fit + (size_t)root * MG_FIT;
-    for (int k = 0; k < MG_FIT; ++k) f[k] = 0;
-    // global position of hit h (computed by k_mg_hits)
-    auto hit_xy = [&](uint32_t h, double& X, double& Y) {
-      X = hxy[2 * (size_t)h];
-      Y = hxy[2 * (size_t)h + 1];
+    double out[MG_FIT] = {};
+    auto store = [&] {
+#pragma unroll
+      for (int k = 0; k < MG_FIT; ++k)
+        if (q == k % G) f[k] = out[k];
     };
-    auto hit_range = [&](uint32_t j, uint32_t& h0, uint32_t& h1) {
-      h0 = hit_start[j];
-      h1 = hit_start[j + 1];
-      if (h1 > hit_cap) h1 = hit_cap;
-      if (h0 > h1) h0 = h1;
+    // step(p, z, cnt): this lane's hit of the next cnt, loaded a step ahead
+    auto each = [&](auto with_z, auto&& step) {
+      for (uint32_t m = i; m < end; ++m) {
+        const uint32_t j = sidx[m], h0 = hit_start[j];
+        const uint32_t h1 = min(hit_start[j + 1], hit_cap);
+        if (h0 >= h1) continue;
+        double2 p = xy[min(h0 + q, h1 - 1)];
+        int32_t z = with_z ? hz[min(h0 + q, h1 - 1)] : 0;
+        for (uint32_t h = h0; h < h1; h += G) {
+          const uint32_t hn = min(h + G + q, h1 - 1);
+          const double2 pn = xy[hn];
+          const int32_t zn = with_z ? hz[hn] : 0;
+          step(p, z, min(h1 - h, G));
+          p = pn;
+          z = zn;
+        }
+      }
     };
-    // every pass loads the next hit's data one hit ahead of its use (same
-    // order of the sums)
-    double sx = 0, sy = 0;
+    double sum = 0, x[G], y[G];
     int64_t nh = 0;
-    for (uint32_t m = i; m < end; ++m) {
-      uint32_t h0, h1;
-      hit_range(sidx[m], h0, h1);
-      double Xn = 0, Yn = 0;
-      if (h0 < h1) hit_xy(h0, Xn, Yn);
-      for (uint32_t h = h0; h < h1; ++h) {
-        const double X = Xn, Y = Yn;
-        if (h + 1 < h1) hit_xy(h + 1, Xn, Yn);
-        sx += X;
-        sy += Y;
-        ++nh;
-      }
-    }
-    f[0] = (double)(end - i);
-    f[1] = (double)nh;
-    const double mx = nh ? sx / nh : 0, my = nh ? sy / nh : 0;
-    double suu = 0, svv = 0, suv = 0, suuu = 0, svvv = 0, suvv = 0, svuu = 0;
-    for (uint32_t m = i; m < end; ++m) {
-      uint32_t h0, h1;
-      hit_range(sidx[m], h0, h1);
-      double Xn = 0, Yn = 0;
-      if (h0 < h1) hit_xy(h0, Xn, Yn);
-      for (uint32_t h = h0; h < h1; ++h) {
-        const double X = Xn, Y = Yn;
-        if (h + 1 < h1) hit_xy(h + 1, Xn, Yn);
-        const double u = X - mx, v = Y - my;
-        suu += u * u;
-        svv += v * v;
-        suv += u * v;
-        suuu += u * u * u;
-        svvv += v * v * v;
-        suvv += u * v * v;
-        svuu += v * u * u;
-      }
-    }
+    each(std::false_type(), [&](const double2& p, int32_t, uint32_t cnt) {
+      const bool have = q < cnt;
+      lds[0][q] = have ? p.x : 0.0;
+      lds[1][q] = have ? p.y : 0.0;
+      nh += cnt;
+      in_order();
+      mg_row(lds[q & 1], x);
+      in_order();
+#pragma unroll
+      for (int k = 0; k < G; ++k) sum += x[k];
+    });
+    out[0] = (double)(end - i);
+    out[1] = (double)nh;
+    const double mx = nh ? of_lane(sum, 0) / nh : 0, my = nh ? of_lane(sum, 1) / nh : 0;
+    sum = 0;
+    each(std::false_type(), [&](const double2& p, int32_t, uint32_t cnt) {
+      const bool have = q < cnt;
+      const double u = have ? p.x - mx : 0.0, v = have ? p.y - my : 0.0;
+      lds[0][q] = u;
+      lds[1][q] = v;
+      lds[2][q] = u * u;
+      lds[3][q] = v * v;
+      lds[4][q] = u * v;
+      in_order();
+      mg_row(lds[fa], x);
+      mg_row(lds[fb], y);
+      in_order();
+#pragma unroll
+      for (int k = 0; k < G; ++k) sum = fma(x[k], y[k], sum);
+    });
+    const double suu = of_lane(sum, 0), svv = of_lane(sum, 1), suv = of_lane(sum, 2);
+    const double suuu = of_lane(sum, 3), svvv = of_lane(sum, 4), suvv = of_lane(sum, 5);
+    const double svuu = of_lane(sum, 6);
     const double det = suu * svv - suv * suv;
-    if (nh < 3 || !(fabs(det) > 0)) continue;
+    if (nh < 3 || !(fabs(det) > 0)) {
+      store();
+      continue;
+    }
     const double b1 = 0.5 * (suuu + suvv), b2 = 0.5 * (svvv + svuu);
     const double uc = (b1 * svv - b2 * suv) / det, vc = (suu * b2 - suv * b1) / det;
     const double xc = mx + uc, yc = my + vc;
-    f[2] = xc;
-    f[3] = yc;
-    f[4] = sqrt(uc * uc + vc * vc + (suu + svv) / nh);
-    f[9] = 1;
-    double psi_prev = 0, acc = 0, sp = 0, sp2 = 0, sz = 0, szp = 0, pmin = 0, pmax = 0;
-    int64_t k = 0;
-    for (uint32_t m = i; m < end; ++m) {
-      uint32_t h0, h1;
-      hit_range(sidx[m], h0, h1);
-      double Xn = 0, Yn = 0;
-      int32_t zn = 0;
-      if (h0 < h1) {
-        hit_xy(h0, Xn, Yn);
-        zn = z_fx[hits[h0]];
+    out[2] = xc;
+    out[3] = yc;
+    out[4] = sqrt(uc * uc + vc * vc + (suu + svv) / nh);
+    out[9] = 1;
+    double psi_prev = 0, acc = 0, pmin = 0, pmax = 0;
+    bool first = true;
+    sum = 0;
+    each(std::true_type(), [&](const double2& p, int32_t z, uint32_t cnt) {
+      // (a lane past the last hit repeats that hit)
+      const double psi = atan2(p.y - yc, p.x - xc);
+      const double up = __shfl_up(psi, 1, G);
+      lds[0][q] = (q == 0 && first) || q >= cnt ? 0.0 : mg_wrap(psi - (q == 0 ? psi_prev : up));
+      first = false;
+      psi_prev = of_lane(psi, G - 1);
+      in_order();
+      mg_row(lds[0], x);
+      in_order();
+      // the azimuth up to this lane's hit, steps added in order
+      double a = 0;
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        acc += x[k];
+        if (q == k) a = acc;
       }
-      for (uint32_t h = h0; h < h1; ++h) {
-        const double X = Xn, Y = Yn;
-        const int32_t zq = zn;
-        if (h + 1 < h1) {
-          hit_xy(h + 1, Xn, Yn);
-          zn = z_fx[hits[h + 1]];
-        }
-        const double psi = atan2(Y - yc, X - xc);
-        acc = k == 0 ? 0.0 : acc + mg_wrap(psi - psi_prev);
-        psi_prev = psi;
-        const double z = zq / 65536.0;
-        sp += acc;
-        sp2 += acc * acc;
-        sz += z;
-        szp += z * acc;
-        if (k == 0 || acc < pmin) pmin = acc;
-        if (k == 0 || acc > pmax) pmax = acc;
-        ++k;
-      }
+      if (a < pmin) pmin = a;
+      if (a > pmax) pmax = a;
+      const bool have = q < cnt;
+      lds[0][q] = have ? a : 0.0;
+      lds[1][q] = have ? z / 65536.0 : 0.0;
+      in_order();
+      mg_row(lds[q >> 1 & 1], x);
+      mg_row(lds[q & 1 ? 0 : 5], y);
+      in_order();
+      // acc, acc acc, z, z acc
+#pragma unroll
+      for (int k = 0; k < G; ++k) sum = fma(x[k], y[k], sum);
+    });
+#pragma unroll
+    for (int k = 1; k < G; k *= 2) {
+      const double lo = __shfl_xor(pmin, k, G), hi = __shfl_xor(pmax, k, G);
+      if (lo < pmin) pmin = lo;
+      if (hi > pmax) pmax = hi;
     }
-    const double dd = k * sp2 - sp * sp;
-    if (!(dd > 0)) continue;
-    const double slope = (k * szp - sp * sz) / dd, icpt = (sz - slope * sp) / k;
-    f[5] = slope;
-    f[8] = fabs(slope) / f[4];
-    f[10] = pmax - pmin;
+    const double sp = of_lane(sum, 0), sp2 = of_lane(sum, 1), sz = of_lane(sum, 2);
+    const double szp = of_lane(sum, 3);
+    const double dd = nh * sp2 - sp * sp;
+    if (!(dd > 0)) {
+      store();
+      continue;
+    }
+    const double slope = (nh * szp - sp * sz) / dd, icpt = (sz - slope * sp) / nh;
+    out[5] = slope;
+    out[8] = fabs(slope) / out[4];
+    out[10] = pmax - pmin;
     if (pmax - pmin < 2 * M_PI) {
       const double psi0 = atan2(-yc, -xc);
       double a = acc + mg_wrap(psi0 - psi_prev);
@@ -539,11 +676,33 @@ __global__ __launch_bounds__(64) void k_mg_fit(const uint32_t* __restrict__ skey
         while (a + 2 * M_PI <= pmin) a += 2 * M_PI;
       }
       const double zd0 = icpt + slope * a;
-      f[6] = zd0;
-      f[7] = 2.0 * (zd0 - 250.0);
-      f[9] = 3;
+      out[6] = zd0;
+      out[7] = 2.0 * (zd0 - 250.0);
+      out[9] = 3;
     }
+    store();
   }
+}
+
+// Bound by the FP64 instructions and the LDS traffic on large frames, where 8
+// lanes per component waste fewer of both (half of 16 have no sum to add up),
+// and on small ones by the longest component, whose hits are one chain that 16
+// lanes shorten: on 139,000 segments 240 us with 8 lanes, 305 with 16 and 566
+// with one; the whole call on one collision 128, 111 and 350 us.
+#define MG_FIT_WIDE 32768  // segments from which 8 lanes take a component
+__global__ __launch_bounds__(64) void k_mg_fit(const uint32_t* __restrict__ skey,
+                                               const uint32_t* __restrict__ sidx,
+                                               const uint32_t* n_trk_dev, uint32_t trk_cap,
+                                               const uint32_t* __restrict__ hit_start,
+                                               uint32_t hit_cap, const double* __restrict__ hxy,
+                                               const int32_t* __restrict__ hz,
+                                               double* __restrict__ fit, const DevStatus* st) {
+  __shared__ __align__(16) double rows[8 * 6 * 10];
+  static_assert(8 * 6 * 10 >= 4 * 6 * 18, "LDS of both widths");
+  if (failed(st)) return;
+  const uint32_t n = scan_count(n_trk_dev, trk_cap);
+  if (n >= MG_FIT_WIDE) mg_fit_rows<8>(skey, sidx, n, hit_start, hit_cap, hxy, hz, fit, rows);
+  else mg_fit_rows<16>(skey, sidx, n, hit_start, hit_cap, hxy, hz, fit, rows);
 }
 
 // The cell table's closing entry (the scan's total).

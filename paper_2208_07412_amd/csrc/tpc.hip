@@ -102,7 +102,9 @@ struct tpc_ctx {
            *mg_idx = nullptr, *mg_skey = nullptr, *mg_sidx = nullptr;
   uint8_t* mg_sector = nullptr;
   double *mg_C = nullptr, *mg_tgl = nullptr, *mg_e = nullptr, *mg_cs18 = nullptr;
-  double *mg_pk = nullptr, *mg_hxy = nullptr;  // ends' gate data in cell order; hit positions
+  MgPos* mg_pos = nullptr;   // ends in cell order
+  MgDir* mg_dir = nullptr;
+  double* mg_hxy = nullptr;  // hit positions
   size_t bsum_cap = 0;
   tpc_tuning tune;
   // stage timing (measurement only)
@@ -131,7 +133,7 @@ struct Plan {
   size_t zblk, cblk, win, cl_list, crec, bsum, tot64, tot32, chain_len, cand, start_flag, f_hits, f_state, f_nhits, f_range, f_ok, f_pts, f_key, f_perm, f_bins, f_krow, f_work, f_qnext, pos,
       owner, nkept, r_par, r_cov, r_chi2, r_row, r_flags, trk_index, qc_part, zp_off, cm_a, cm_b, cm_res, cm_tot, cm_info, mg_fs,
       mg_cell, mg_cnt, mg_off, mg_cur, mg_ends, mg_parent, mg_key, mg_idx, mg_skey, mg_sidx,
-      mg_sector, mg_C, mg_tgl, mg_e, mg_cs18, mg_pk, mg_hxy, hit_off, par, st, total;
+      mg_sector, mg_C, mg_tgl, mg_e, mg_cs18, mg_pos, mg_dir, mg_hxy, hit_off, par, st, total;
   size_t bsum_cap;
   uint32_t nblk, nblk_s, nwin;
 };
@@ -227,7 +229,8 @@ Plan plan_for(const tpc_sizes& m) {
   p.mg_tgl = L.add<double>(mt);
   p.mg_e = L.add<double>(10 * mt);
   p.mg_cs18 = L.add<double>(36);
-  p.mg_pk = L.add<double>(6 * mt);
+  p.mg_pos = L.add<MgPos>(2 * mt);
+  p.mg_dir = L.add<MgDir>(2 * mt);
   p.mg_hxy = L.add<double>(2 * mc);
   p.par = L.add<DevParams>(1);
   p.st = L.add<DevStatus>(1);
@@ -899,7 +902,8 @@ int tpc_create(tpc_ctx** out, const tpc_params* p, const tpc_sizes* max, void* h
   c->mg_tgl = (double*)(base + pl.mg_tgl);
   c->mg_e = (double*)(base + pl.mg_e);
   c->mg_cs18 = (double*)(base + pl.mg_cs18);
-  c->mg_pk = (double*)(base + pl.mg_pk);
+  c->mg_pos = (MgPos*)(base + pl.mg_pos);
+  c->mg_dir = (MgDir*)(base + pl.mg_dir);
   c->mg_hxy = (double*)(base + pl.mg_hxy);
   c->d_par = (DevParams*)(base + pl.par);
   c->d_st = (DevStatus*)(base + pl.st);
@@ -1088,14 +1092,15 @@ int tpc_merge_tracks(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, t
   k_mg_total<<<1, 1, 0, s>>>(c->mg_off, c->tot32, n_cells, c->d_st);
   k_mg_fill_cells<<<grid_for(2 * (uint64_t)cap, 256, 4096), 256, 0, s>>>(
       c->mg_cell, tr->n_tracks, cap, c->mg_cur, c->mg_ends, c->d_st);
-  k_mg_pack<<<grid_for(2 * (uint64_t)cap, 256, 4096), 256, 0, s>>>(c->mg_ends, c->tot32, c->mg_e,
-                                                                   c->mg_pk, c->d_st);
-  k_mg_pairs<<<grid_for(2 * (uint64_t)cap, 256, 8192), 256, 0, s>>>(
-      S, nzb, c->tot32, c->mg_off, c->mg_ends, c->mg_cell, c->mg_pk, c->mg_parent, out->near_tie,
+  k_mg_pack<<<grid_for(2 * (uint64_t)cap, 256, 4096), 256, 0, s>>>(c->mg_ends, c->tot32, S,
+                                                                   c->mg_pos, c->mg_dir, c->d_st);
+  k_mg_pairs<<<grid_for(2 * (uint64_t)cap * MG_RUNS, 256, MG_PAIR_BLOCKS), 256, 0, s>>>(
+      S, nzb, c->tot32, c->mg_off, c->mg_cell, c->mg_pos, c->mg_dir, c->mg_parent, out->near_tie,
       c->d_st);
   k_mg_hits<<<grid_for(hit_bound, 256, 16384), 256, 0, s>>>(
-      cl->crow_start, n_ur, cl->y_fx, cl->n_clusters, cl->capacity, tr->hit_start, tr->hits,
-      hit_bound, tr->n_tracks, cap, c->mg_cs18, c->mg_hxy, c->d_par, c->d_st);
+      cl->crow_start, n_ur, cl->y_fx, cl->z_fx, cl->n_clusters, cl->capacity, tr->hit_start,
+      tr->hits, hit_bound, tr->n_tracks, cap, c->mg_cs18, c->mg_hxy,
+      reinterpret_cast<int32_t*>(c->cm_res), c->d_par, c->d_st);
   k_mg_labels<<<grid_for(cap, 256, 4096), 256, 0, s>>>(c->mg_parent, tr->n_tracks, cap, out->label,
                                                        c->mg_key, c->d_st);
   // members grouped by component in ascending index: labels are below 2^24
@@ -1118,9 +1123,9 @@ int tpc_merge_tracks(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, t
     }
     // three passes: the result is in (mg_skey, mg_sidx)
   }
-  k_mg_fit<<<grid_for(cap, 64, 16384), 64, 0, s>>>(c->mg_skey, c->mg_sidx, tr->n_tracks, cap,
-                                                   cl->z_fx, tr->hit_start, tr->hits, hit_bound,
-                                                   c->mg_hxy, out->fit, c->d_st);
+  k_mg_fit<<<grid_for(cap, 4, 65536), 64, 0, s>>>(
+      c->mg_skey, c->mg_sidx, tr->n_tracks, cap, tr->hit_start, hit_bound, c->mg_hxy,
+      reinterpret_cast<const int32_t*>(c->cm_res), out->fit, c->d_st);
   run_count<uint32_t>(c, MgIsRoot{out->label}, tr->n_tracks, cap, out->n_merged);
   return launch_ok();
 }
