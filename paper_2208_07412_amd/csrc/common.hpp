@@ -203,22 +203,82 @@ __device__ __forceinline__ T block_excl_scan(T v, T* lds, T& total) {
   return res;
 }
 
-// ------------------------------------------------- device-wide scan (3 phases)
+// ----------------------------------------------------------- device-wide scan
 // Get:  T operator()(uint32_t i) const -- value of element i (i < n)
 // Emit: void operator()(uint32_t i, T prefix, T value) const
+// Fin:  void operator()(T total) const -- called once, by one thread
 // The element count is min(*n_dev, n_cap) when n_dev is given, else n_cap.
+// Three forms, by n_cap (a launch takes at least 4.6 us back to back): one
+// workgroup for up to SCAN_ONE elements; sums of tiles, then a pass whose
+// workgroups add up the sums before theirs, for up to SCAN_SELF tiles (a
+// workgroup reads them in SCAN_SELF / 256 steps); beyond, the sums are scanned
+// by a launch of their own.
+#define SCAN_ONE 16384
+#define SCAN_SELF 2048
 __device__ __forceinline__ uint32_t scan_count(const uint32_t* n_dev, uint32_t n_cap) {
   if (!n_dev) return n_cap;
   const uint32_t n = *n_dev;
   return n < n_cap ? n : n_cap;
 }
 
+struct NoFin {
+  template <typename T>
+  __device__ void operator()(T) const {}
+};
+template <typename T>
+struct StoreFin {  // the total, to memory
+  T* out;
+  __device__ void operator()(T total) const { *out = total; }
+};
+
+// the ordered scan of SCAN_ITEMS consecutive elements per thread from `first`,
+// whose prefix is `pre` plus that of the threads before; the workgroup's total
+template <int BLOCK, typename T, class Get, class Emit>
+__device__ __forceinline__ T scan_tile(const Get& get, const Emit& emit, uint32_t first, uint32_t n,
+                                       T pre, T* lds) {
+  T vals[SCAN_ITEMS];
+  T acc = 0;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    const uint32_t i = first + k;
+    vals[k] = i < n ? get(i) : T(0);
+    acc += vals[k];
+  }
+  T total;
+  pre += block_excl_scan<T, BLOCK>(acc, lds, total);
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    const uint32_t i = first + k;
+    if (i < n) emit(i, pre, vals[k]);
+    pre += vals[k];
+  }
+  return total;
+}
+
+template <typename T, class Get, class Emit, class Fin>
+__global__ __launch_bounds__(1024) void k_scan_one(Get get, Emit emit, Fin fin,
+                                                   const uint32_t* n_dev, uint32_t n_cap,
+                                                   const DevStatus* st) {
+  __shared__ T lds[1024 / 64 + 1];
+  if (failed(st)) return;
+  const uint32_t n = scan_count(n_dev, n_cap);
+  T carry = 0;
+  for (uint32_t base = 0; base < n; base += 1024 * SCAN_ITEMS)
+    carry += scan_tile<1024>(get, emit, base + threadIdx.x * SCAN_ITEMS, n, carry, lds);
+  if (threadIdx.x == 0) fin(carry);
+}
+
+// bsum[workgroup] = its tile's sum; bsum[gridDim.x] = 1, or 0 after a latched
+// error (the last pass goes by this word: fin may latch an error itself while
+// other workgroups of its launch still start)
 template <typename T, class Get>
 __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_reduce(Get get, const uint32_t* n_dev,
                                                             uint32_t n_cap, T* bsum,
                                                             const DevStatus* st) {
   __shared__ T lds[SCAN_BLOCK / 64 + 1];
-  if (failed(st)) return;
+  const bool ok = !failed(st);
+  if (blockIdx.x == 0 && threadIdx.x == 0) bsum[gridDim.x] = ok ? 1 : 0;
+  if (!ok) return;
   const uint32_t n = scan_count(n_dev, n_cap);
   const uint32_t base = blockIdx.x * SCAN_TILE;
   T acc = 0;
@@ -236,8 +296,7 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_reduce(Get get, const uint3
 
 // Exclusive scan of the block sums in place, by one workgroup of 1024.
 template <typename T>
-__global__ __launch_bounds__(1024) void k_scan_blocks(T* bsum, uint32_t nb, T* total_out,
-                                                      uint32_t* total32_out, const DevStatus* st) {
+__global__ __launch_bounds__(1024) void k_scan_blocks(T* bsum, uint32_t nb, const DevStatus* st) {
   __shared__ T lds[1024 / 64 + 1];
   if (failed(st)) return;
   T carry = 0;
@@ -249,51 +308,33 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(T* bsum, uint32_t nb, T* t
     if (i < nb) bsum[i] = carry + ex;
     carry += tot;
   }
-  if (threadIdx.x == 0) {
-    if (total_out) *total_out = carry;
-    if (total32_out) *total32_out = (uint32_t)carry;
-  }
 }
 
-template <typename T, class Get, class Emit>
-__global__ __launch_bounds__(SCAN_BLOCK) void k_scan_down(Get get, Emit emit, const uint32_t* n_dev,
-                                                          uint32_t n_cap, const T* bsum,
-                                                          const DevStatus* st) {
+// SELF: bsum still holds the tiles' sums, not their scan
+template <bool SELF, typename T, class Get, class Emit, class Fin>
+__global__ __launch_bounds__(SCAN_BLOCK) void k_scan_down(Get get, Emit emit, Fin fin,
+                                                          const uint32_t* n_dev, uint32_t n_cap,
+                                                          const T* bsum) {
   __shared__ T lds[SCAN_BLOCK / 64 + 1];
-  if (failed(st)) return;
+  if (bsum[gridDim.x] == 0) return;
   const uint32_t n = scan_count(n_dev, n_cap);
   const uint32_t base = blockIdx.x * SCAN_TILE;
-  if (base >= n) return;  // uniform per block
-  // each thread owns SCAN_ITEMS consecutive elements for an ordered scan
-  const uint32_t first = base + threadIdx.x * SCAN_ITEMS;
-  T vals[SCAN_ITEMS];
-  T acc = 0;
-#pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
-    const uint32_t i = first + k;
-    vals[k] = i < n ? get(i) : T(0);
-    acc += vals[k];
+  const bool last = blockIdx.x + 1 == gridDim.x;
+  if (base >= n && !last) return;  // uniform per block
+  T pre;
+  if (SELF) {
+    T acc = 0;
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += SCAN_BLOCK) acc += bsum[i];
+    block_excl_scan<T, SCAN_BLOCK>(acc, lds, pre);
+  } else {
+    pre = bsum[blockIdx.x];
   }
-  T total;
-  T pre = block_excl_scan<T, SCAN_BLOCK>(acc, lds, total) + bsum[blockIdx.x];
-#pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
-    const uint32_t i = first + k;
-    if (i < n) emit(i, pre, vals[k]);
-    pre += vals[k];
-  }
+  const T total = scan_tile<SCAN_BLOCK>(get, emit, base + threadIdx.x * SCAN_ITEMS, n, pre, lds);
+  if (last && threadIdx.x == 0) fin(pre + total);
 }
 
 template <typename T>
 __global__ void k_fill(T* p, T v, uint32_t n) {
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-// fill the first min(*n_dev, n_cap) entries
-template <typename T>
-__global__ void k_fill_dev(T* p, T v, const uint32_t* n_dev, uint32_t n_cap) {
-  const uint32_t n = scan_count(n_dev, n_cap);
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
     p[i] = v;
 }

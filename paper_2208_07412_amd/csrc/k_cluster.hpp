@@ -73,21 +73,19 @@ __device__ __forceinline__ void bi_sample(uint32_t s, uint32_t t, int32_t prev, 
 // and 0.275 ms with 1, 4, 8 and 16 parts)
 #define BI_PARTS 4
 template <bool USE_LDS>
-__global__ __launch_bounds__(256) void k_block_index(const uint16_t* __restrict__ tkey,
-                                                     const uint16_t* __restrict__ pkey,
-                                                     const uint16_t* __restrict__ akey,
-                                                     const uint32_t* __restrict__ rstart,
-                                                     uint32_t n_ur, uint32_t nblk, uint32_t bshift,
-                                                     uint32_t T, uint32_t n_total,
-                                                     uint32_t* __restrict__ blk,
-                                                     const DevParams* __restrict__ P,
-                                                     DevStatus* st, int check_input) {
+__device__ __forceinline__ void block_index(const uint16_t* __restrict__ tkey,
+                                            const uint16_t* __restrict__ pkey,
+                                            const uint16_t* __restrict__ akey,
+                                            const uint32_t* __restrict__ rstart, uint32_t n_ur,
+                                            uint32_t nblk, uint32_t bshift, uint32_t T,
+                                            uint32_t n_total, uint32_t* __restrict__ blk,
+                                            const DevParams* __restrict__ P, DevStatus* st,
+                                            int check_input, uint32_t nwg) {
   __shared__ uint32_t lt[USE_LDS ? BI_LDS : 1];
-  if (failed(st)) return;
   const bool vec = ((uintptr_t)tkey & 15) == 0 && (!check_input || ((uintptr_t)pkey & 15) == 0);
   const bool staged = USE_LDS && nblk + 1 <= BI_LDS;
   constexpr uint32_t parts = USE_LDS ? 1 : BI_PARTS;
-  for (uint32_t item = blockIdx.x; item < n_ur * parts; item += gridDim.x) {
+  for (uint32_t item = blockIdx.x; item < n_ur * parts; item += nwg) {
     const uint32_t ur = item / parts, part = item % parts;
     uint32_t s0 = rstart[ur], s1 = rstart[ur + 1];
     if (s1 > n_total) s1 = n_total;
@@ -191,6 +189,16 @@ __global__ __launch_bounds__(256) void k_block_index(const uint16_t* __restrict_
       for (uint32_t k = threadIdx.x; k <= nblk; k += blockDim.x) bg[k] = lt[k];
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_sample_index(
+    const uint16_t* __restrict__ tkey, const uint16_t* __restrict__ pkey,
+    const uint16_t* __restrict__ akey, const uint32_t* __restrict__ rstart, uint32_t n_ur,
+    uint32_t nblk, uint32_t T, uint32_t n_total, uint32_t* __restrict__ blk,
+    const DevParams* __restrict__ P, DevStatus* st) {
+  if (failed(st)) return;
+  block_index<false>(tkey, pkey, akey, rstart, n_ur, nblk, CL_BSHIFT, T, n_total, blk, P, st, 1,
+                     gridDim.x);
 }
 
 // After an input error the block table may be inconsistent; clamp it so that
@@ -1466,22 +1474,29 @@ __global__ __launch_bounds__(256) void k_cluster_output(const uint32_t* __restri
   }
 }
 
-// crow_start[ur] = first cluster of (unit,row), from the scanned window
-// counts (nwin windows per unit-row).
-__global__ void k_crow_start(const uint32_t* __restrict__ win_off, uint32_t nwin,
-                             uint32_t n_ur, const uint32_t* __restrict__ n_clusters,
-                             uint32_t capacity, uint32_t* __restrict__ crow, DevStatus* st) {
-  // after a latched error the scan that wrote *n_clusters did not run
-  if (failed(st)) return;
-  const uint32_t n = *n_clusters;
-  for (uint32_t ur = blockIdx.x * blockDim.x + threadIdx.x; ur <= n_ur;
-       ur += gridDim.x * blockDim.x)
-    crow[ur] = ur < n_ur ? win_off[(size_t)ur * nwin] : n;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+// The scan of the window counts (nwin windows per unit-row) leaves every
+// window's first cluster in place and crow_start[ur], the first cluster of each
+// unit-row, then the count.
+struct EmitWindow {
+  uint32_t *win, *crow;
+  uint32_t nwin;
+  __device__ void operator()(uint32_t i, uint32_t pre, uint32_t) const {
+    win[i] = pre;
+    const uint32_t ur = i / nwin;
+    if (ur * nwin == i) crow[ur] = pre;
+  }
+};
+struct FinClusters {
+  uint32_t *crow_end, *n_clusters;
+  uint32_t capacity;
+  DevStatus* st;
+  __device__ void operator()(uint32_t n) const {
+    *crow_end = n;
+    *n_clusters = n;
     st->n_clusters = n;
     if (n > capacity) latch_capacity(st, OVF_CLUSTERS, n);
   }
-}
+};
 
 // Replace the packed peak position of every sample by its cluster id
 // (binary search among the row's clusters, which are sorted by peak).

@@ -25,21 +25,36 @@ struct ClusterView {
   }
 };
 
-// Packed copy of the fixed-point positions for the search kernels.
-__global__ void k_pack_pos(const int32_t* __restrict__ y, const int32_t* __restrict__ z,
-                           const uint32_t* n_dev, uint32_t n_cap, int2* __restrict__ pos,
-                           const DevStatus* st) {
-  if (failed(st)) return;
-  const uint32_t n = scan_count(n_dev, n_cap);
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    pos[i] = make_int2(y[i], z[i]);
-}
-
 // The cluster grid (block index over peak times) has one entry per
 // 2^CG_BSHIFT time bins.
 #ifndef CG_BSHIFT
 #define CG_BSHIFT 1
 #endif
+
+// What the searches need of the clusters, in one launch: the first n_ur
+// workgroups build the cluster grid, the others pack the fixed-point positions
+// and clear the claims.
+__global__ __launch_bounds__(256) void k_hit_grid(ClusterView cl, const uint16_t* __restrict__ ppad,
+                                                  uint32_t n_ur, uint32_t nblk, uint32_t T,
+                                                  uint32_t* __restrict__ blk,
+                                                  const int32_t* __restrict__ y,
+                                                  const int32_t* __restrict__ z,
+                                                  int2* __restrict__ pos,
+                                                  uint32_t* __restrict__ owner,
+                                                  const DevParams* __restrict__ P, DevStatus* st) {
+  if (failed(st)) return;
+  if (blockIdx.x < n_ur) {
+    block_index<true>(cl.ptime, ppad, nullptr, cl.crow, n_ur, nblk, CG_BSHIFT, T, cl.capacity, blk,
+                      P, st, 0, n_ur);
+    return;
+  }
+  const uint32_t n = scan_count(cl.n_clusters, cl.capacity);
+  for (uint32_t i = (blockIdx.x - n_ur) * blockDim.x + threadIdx.x; i < n;
+       i += (gridDim.x - n_ur) * blockDim.x) {
+    pos[i] = make_int2(y[i], z[i]);
+    owner[i] = 0;
+  }
+}
 
 // Candidate cluster range of row ur for a drift position z (fixed point):
 // |z_c - z| <= win_z and the centroid lies within 2 bins of the peak time.
@@ -317,12 +332,13 @@ struct EmitTracklet {
   }
 };
 
-__global__ void k_tracklet_count(const uint32_t* n_tl, uint32_t capacity, uint32_t* out_n,
-                                 DevStatus* st) {
-  // after a latched error the scan that wrote *n_tl did not run
-  if (failed(st)) return;
-  const uint32_t n = *n_tl;
-  st->n_tracklets = n;
-  if (out_n) *out_n = n;
-  if (n > capacity) latch_capacity(st, OVF_TRACKLETS, n);
-}
+struct FinTracklets {
+  uint32_t capacity;
+  uint32_t* out_n;
+  DevStatus* st;
+  __device__ void operator()(uint32_t n) const {
+    st->n_tracklets = n;
+    if (out_n) *out_n = n;
+    if (n > capacity) latch_capacity(st, OVF_TRACKLETS, n);
+  }
+};

@@ -138,19 +138,6 @@ __global__ void k_mg_segments(const uint32_t* __restrict__ crow, uint32_t n_ur,
   }
 }
 
-// ends into their cells (any order within a cell: the unions do not depend on it)
-__global__ void k_mg_fill_cells(const uint32_t* __restrict__ cell_of_end, const uint32_t* n_trk_dev,
-                                uint32_t trk_cap, uint32_t* __restrict__ cursor,
-                                uint32_t* __restrict__ cell_ends, const DevStatus* st) {
-  if (failed(st)) return;
-  const uint32_t n_ends = 2 * scan_count(n_trk_dev, trk_cap);  // only this call's ends
-  for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n_ends; e += gridDim.x * blockDim.x) {
-    const uint32_t c = cell_of_end[e];
-    if (c == 0xFFFFFFFFu) continue;
-    cell_ends[atomicAdd(&cursor[c], 1u)] = e;
-  }
-}
-
 __device__ __forceinline__ uint32_t mg_find(const uint32_t* parent, uint32_t x) {
   uint32_t p = __atomic_load_n(&parent[x], __ATOMIC_RELAXED);
   while (p != x) {
@@ -216,14 +203,20 @@ struct MgPos {
 struct MgDir {
   float tx, ty, C, tgl;
 };
-__global__ void k_mg_pack(const uint32_t* __restrict__ cell_ends, const uint32_t* total_dev,
-                          MgSegs S, MgPos* __restrict__ pos, MgDir* __restrict__ dir,
-                          const DevStatus* st) {
+// The ends into their cells (in any order within a cell: the unions do not
+// depend on it).
+__global__ void k_mg_fill_cells(const uint32_t* __restrict__ cell_of_end, const uint32_t* n_trk_dev,
+                                uint32_t trk_cap, uint32_t* __restrict__ cursor, MgSegs S,
+                                MgPos* __restrict__ pos, MgDir* __restrict__ dir,
+                                const DevStatus* st) {
   if (failed(st)) return;
-  const uint32_t total = *total_dev;
-  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < total; k += gridDim.x * blockDim.x) {
-    const uint32_t e = cell_ends[k], j = e >> 1;
+  const uint32_t n_ends = 2 * scan_count(n_trk_dev, trk_cap);  // only this call's ends
+  for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n_ends;
+       e += gridDim.x * blockDim.x) {
+    const uint32_t c = cell_of_end[e], j = e >> 1;
+    if (c == 0xFFFFFFFFu) continue;
     const double* E = S.e + (size_t)j * 10 + 5 * (e & 1);
+    const uint32_t k = atomicAdd(&cursor[c], 1u);
     pos[k] = MgPos{(float)E[0], (float)E[1], (int32_t)(E[2] * 65536.0), e};
     dir[k] = MgDir{(float)E[3], (float)E[4], (float)S.C[j], (float)S.tgl[j]};
   }
@@ -471,39 +464,53 @@ __global__ void k_mg_hits(const uint32_t* __restrict__ crow, uint32_t n_ur,
   }
 }
 
-__global__ void k_mg_init(uint32_t* __restrict__ parent, uint8_t* __restrict__ near_tie,
-                          uint32_t* __restrict__ idx, uint32_t cap, const DevStatus* st) {
+// Everything that the call starts from: no ends in the cells, every segment a
+// root, fit records (n_fit doubles) and the count of merged tracks zero.
+__global__ void k_mg_init(uint32_t* __restrict__ cell_cnt, uint32_t n_cells,
+                          double* __restrict__ fit, uint32_t n_fit, uint32_t* __restrict__ parent,
+                          uint8_t* __restrict__ near_tie, uint32_t* __restrict__ idx, uint32_t cap,
+                          uint32_t* __restrict__ n_merged, const DevStatus* st) {
+  const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, di = gridDim.x * blockDim.x;
+  for (uint32_t i = i0; i < n_fit; i += di) fit[i] = 0.0;
   if (failed(st)) return;
-  for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < cap; j += gridDim.x * blockDim.x) {
+  for (uint32_t i = i0; i < n_cells; i += di) cell_cnt[i] = 0;
+  for (uint32_t j = i0; j < cap; j += di) {
     parent[j] = j;
     near_tie[j] = 0;
     idx[j] = j;
   }
+  if (i0 == 0) *n_merged = 0;
 }
 
-// label = the root; also counts the components (roots) by a reduction's input
-__global__ void k_mg_labels(const uint32_t* __restrict__ parent, const uint32_t* n_trk_dev,
-                            uint32_t trk_cap, int32_t* __restrict__ label,
-                            uint32_t* __restrict__ key, const DevStatus* st) {
+// label = the root; the roots are counted, one atomic per workgroup.
+__global__ __launch_bounds__(256) void k_mg_labels(const uint32_t* __restrict__ parent,
+                                                   const uint32_t* n_trk_dev, uint32_t trk_cap,
+                                                   int32_t* __restrict__ label,
+                                                   uint32_t* __restrict__ key,
+                                                   uint32_t* __restrict__ n_merged,
+                                                   const DevStatus* st) {
+  __shared__ uint32_t roots;
   if (failed(st)) return;
+  if (threadIdx.x == 0) roots = 0;
+  __syncthreads();
   const uint32_t n = scan_count(n_trk_dev, trk_cap);
-  for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < trk_cap; j += gridDim.x * blockDim.x) {
-    if (j < n) {
-      const uint32_t r = mg_find(parent, j);
-      label[j] = (int32_t)r;
-      key[j] = r;
-    } else {
-      key[j] = 0xFFFFFFFFu;  // beyond the tracks: sorted to the end
-    }
+  uint32_t mine = 0;
+  for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) {
+    const uint32_t r = mg_find(parent, j);
+    label[j] = (int32_t)r;
+    key[j] = r;
+    mine += r == j;
   }
+  if (mine) atomicAdd(&roots, mine);
+  __syncthreads();
+  if (threadIdx.x == 0 && roots) atomicAdd(n_merged, roots);
 }
 
-// The lanes' values of one array, in the lanes' order.
-template <int G>
-__device__ __forceinline__ void mg_row(const double* lds, double (&x)[G]) {
+// Eight lanes' values of one array, in the lanes' order.
+__device__ __forceinline__ void mg_row(const double* lds, double (&x)[8]) {
   const double2* v = reinterpret_cast<const double2*>(lds);
 #pragma unroll
-  for (int i = 0; i < G / 2; ++i) {
+  for (int i = 0; i < 4; ++i) {
     const double2 t = v[i];
     x[2 * i] = t.x;
     x[2 * i + 1] = t.y;
@@ -568,7 +575,18 @@ __device__ __forceinline__ void mg_fit_rows(const uint32_t* __restrict__ skey,
         }
       }
     };
-    double sum = 0, x[G], y[G];
+    double sum = 0;
+    // adds the products of two arrays in order
+    auto add = [&](const double* a, const double* b) {
+#pragma unroll
+      for (int half = 0; half < G; half += 8) {
+        double x[8], y[8];
+        mg_row(a + half, x);
+        mg_row(b + half, y);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum = fma(x[k], y[k], sum);
+      }
+    };
     int64_t nh = 0;
     each(std::false_type(), [&](const double2& p, int32_t, uint32_t cnt) {
       const bool have = q < cnt;
@@ -576,10 +594,14 @@ __device__ __forceinline__ void mg_fit_rows(const uint32_t* __restrict__ skey,
       lds[1][q] = have ? p.y : 0.0;
       nh += cnt;
       in_order();
-      mg_row(lds[q & 1], x);
-      in_order();
 #pragma unroll
-      for (int k = 0; k < G; ++k) sum += x[k];
+      for (int half = 0; half < G; half += 8) {
+        double x[8];
+        mg_row(lds[q & 1] + half, x);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum += x[k];
+      }
+      in_order();
     });
     out[0] = (double)(end - i);
     out[1] = (double)nh;
@@ -594,11 +616,8 @@ __device__ __forceinline__ void mg_fit_rows(const uint32_t* __restrict__ skey,
       lds[3][q] = v * v;
       lds[4][q] = u * v;
       in_order();
-      mg_row(lds[fa], x);
-      mg_row(lds[fb], y);
+      add(lds[fa], lds[fb]);
       in_order();
-#pragma unroll
-      for (int k = 0; k < G; ++k) sum = fma(x[k], y[k], sum);
     });
     const double suu = of_lane(sum, 0), svv = of_lane(sum, 1), suv = of_lane(sum, 2);
     const double suuu = of_lane(sum, 3), svvv = of_lane(sum, 4), suvv = of_lane(sum, 5);
@@ -626,27 +645,27 @@ __device__ __forceinline__ void mg_fit_rows(const uint32_t* __restrict__ skey,
       first = false;
       psi_prev = of_lane(psi, G - 1);
       in_order();
-      mg_row(lds[0], x);
-      in_order();
       // the azimuth up to this lane's hit, steps added in order
       double a = 0;
 #pragma unroll
-      for (int k = 0; k < G; ++k) {
-        acc += x[k];
-        if (q == k) a = acc;
+      for (int half = 0; half < G; half += 8) {
+        double x[8];
+        mg_row(lds[0] + half, x);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          acc += x[k];
+          if (q == half + k) a = acc;
+        }
       }
+      in_order();
       if (a < pmin) pmin = a;
       if (a > pmax) pmax = a;
       const bool have = q < cnt;
       lds[0][q] = have ? a : 0.0;
       lds[1][q] = have ? z / 65536.0 : 0.0;
       in_order();
-      mg_row(lds[q >> 1 & 1], x);
-      mg_row(lds[q & 1 ? 0 : 5], y);
+      add(lds[q >> 1 & 1], lds[q & 1 ? 0 : 5]);  // acc, acc acc, z, z acc
       in_order();
-      // acc, acc acc, z, z acc
-#pragma unroll
-      for (int k = 0; k < G; ++k) sum = fma(x[k], y[k], sum);
     });
 #pragma unroll
     for (int k = 1; k < G; k *= 2) {
@@ -688,9 +707,11 @@ __device__ __forceinline__ void mg_fit_rows(const uint32_t* __restrict__ skey,
 // lanes per component waste fewer of both (half of 16 have no sum to add up),
 // and on small ones by the longest component, whose hits are one chain that 16
 // lanes shorten: on 139,000 segments 240 us with 8 lanes, 305 with 16 and 566
-// with one; the whole call on one collision 128, 111 and 350 us.
+// with one; the whole call on one small collision 128, 111 and 350 us.  Four waves
+// per SIMD, so the arrays are read eight values at a time: with both widths in the
+// kernel the compiler's own choice of 172 registers took 299 us on the large one.
 #define MG_FIT_WIDE 32768  // segments from which 8 lanes take a component
-__global__ __launch_bounds__(64) void k_mg_fit(const uint32_t* __restrict__ skey,
+__global__ __launch_bounds__(64, 4) void k_mg_fit(const uint32_t* __restrict__ skey,
                                                const uint32_t* __restrict__ sidx,
                                                const uint32_t* n_trk_dev, uint32_t trk_cap,
                                                const uint32_t* __restrict__ hit_start,
@@ -705,22 +726,19 @@ __global__ __launch_bounds__(64) void k_mg_fit(const uint32_t* __restrict__ skey
   else mg_fit_rows<16>(skey, sidx, n, hit_start, hit_cap, hxy, hz, fit, rows);
 }
 
-// The cell table's closing entry (the scan's total).
-__global__ void k_mg_total(uint32_t* __restrict__ off, const uint32_t* total, uint32_t n_cells,
-                           const DevStatus* st) {
-  if (failed(st)) return;
-  off[n_cells] = *total;
-}
-
 // One pass of a stable least-significant-digit radix sort of (key, value)
 // pairs on the 8-bit digit at `shift`: the count step writes, per block of
-// MG_SORT_BLOCK elements, the count of each digit to bins[digit * nb + block];
-// after an exclusive scan of bins, the scatter step places each element at
-// its digit's position, ranking equal digits in index order (a wave's lanes
-// by ballot, the waves of a block one after the other).  Three passes order
-// keys below 2^24 with equal keys in index order.
+// MG_SORT_BLOCK elements, the count of each digit; the scatter step places each
+// element at its digit's position, ranking equal digits in index order (a wave's
+// lanes by ballot, the waves of a block one after the other).  DIRECT (up to
+// MG_SORT_DIRECT blocks, by capacity): the counts are bins[block * 256 + digit] and
+// every block adds up its positions itself; beyond, bins[digit * nb + block] are
+// scanned in place between the steps (a launch or two more, where a block would
+// read more than that many counts per digit).  As many passes as the labels'
+// bits need order them with equal keys in index order.
+#define MG_SORT_DIRECT 512
 #define MG_SORT_BLOCK 1024
-template <bool SCATTER>
+template <bool SCATTER, bool DIRECT>
 __global__ __launch_bounds__(256) void k_mg_rsort(const uint32_t* __restrict__ kin,
                                                   const uint32_t* __restrict__ vin,
                                                   const uint32_t* n_dev, uint32_t cap, int shift,
@@ -749,12 +767,25 @@ __global__ __launch_bounds__(256) void k_mg_rsort(const uint32_t* __restrict__ k
   __syncthreads();
   const uint32_t d = threadIdx.x;
   const uint32_t c0 = h[0][d], c1 = h[1][d], c2 = h[2][d], c3 = h[3][d];
-  const size_t bi = (size_t)d * nb + blockIdx.x;
+  const size_t bi = DIRECT ? (size_t)blockIdx.x * 256u + d : (size_t)d * nb + blockIdx.x;
   if (!SCATTER) {
     bins[bi] = c0 + c1 + c2 + c3;
     return;
   }
-  const uint32_t base = bins[bi];
+  uint32_t base;
+  if (DIRECT) {
+    __shared__ uint32_t lds[256 / 64 + 1];
+    uint32_t all = 0, before = 0, total;
+#pragma unroll 8
+    for (uint32_t l = 0; l < nb; ++l) {
+      const uint32_t v = bins[(size_t)l * 256u + d];
+      all += v;
+      before += l < blockIdx.x ? v : 0u;
+    }
+    base = block_excl_scan<uint32_t, 256>(all, lds, total) + before;
+  } else {
+    base = bins[bi];
+  }
   __syncthreads();
   h[0][d] = base;
   h[1][d] = base + c0;
@@ -782,8 +813,3 @@ __global__ __launch_bounds__(256) void k_mg_rsort(const uint32_t* __restrict__ k
     if (v && (eq >> lane) == 1ull) h[w][dig[j]] += (uint32_t)__popcll(eq);
   }
 }
-
-struct MgIsRoot {
-  const int32_t* label;
-  __device__ uint32_t operator()(uint32_t j) const { return label[j] == (int32_t)j ? 1u : 0u; }
-};

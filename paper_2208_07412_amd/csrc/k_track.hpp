@@ -13,6 +13,8 @@
 #include "k_cluster.hpp"
 #include "k_links.hpp"
 
+#define XCD_GROUPS 8  // sort groups of the following: one per XCD
+
 #define FX_SCALE 1.52587890625e-05  // 2^-16
 
 enum { TF_NOT_PD = 1, TF_REFIT_FAIL = 2, TF_FP64 = 4, TF_FP64_FAIL = 8, TF_TO_FP64 = 16 };
@@ -444,7 +446,13 @@ __global__ __launch_bounds__(256) void k_tracklet_points(ClusterView cl, uint32_
                                                          const uint32_t* n_tl_dev, uint32_t tl_cap,
                                                          uint32_t* __restrict__ pts,
                                                          uint8_t* __restrict__ key,
-                                                         const DevStatus* st) {
+                                                         uint32_t* __restrict__ qnext,
+                                                         DevStatus* st) {
+  // the counters of the fit stage and the queue counters of its following
+  if (blockIdx.x == 0 && threadIdx.x < 2 * XCD_GROUPS) {
+    if (threadIdx.x < 5) (&st->n_fallback)[threadIdx.x] = 0;
+    qnext[threadIdx.x] = 0;
+  }
   if (failed(st)) return;
   const uint32_t n_tl = scan_count(n_tl_dev, tl_cap);
   const uint32_t n_cl = scan_count(cl.n_clusters, cl.capacity);
@@ -492,39 +500,44 @@ __global__ __launch_bounds__(256) void k_tracklet_points(ClusterView cl, uint32_
 // can first split the tracklets into ngrp groups of consecutive blocks (so of
 // consecutive units) and sort each group on its own: the following gives group
 // g to the workgroups that the dispatcher places on XCD g, so each XCD's L2
-// holds the hit data of its own units only.  Three steps: k_sort_work<false>
-// counts each block of SORT_BLOCK tracklets per key into
-// bins[(g * 256 + key') * npg + block in group] (key' = 255 - key, npg blocks per
-// group); an exclusive scan of bins in place gives every (group, key', block)
-// its first position, and bins[g * 256 * npg] is where group g starts;
-// k_sort_work<true> writes perm, ranking the elements of one key in index
-// order.  Tracklets of equal estimate keep their order (unit, row, time), so
-// neighbouring tracks share a wave.  Wave w of a workgroup takes the elements
+// holds the hit data of its own units only.  Steps: k_sort_work<false>
+// counts each block of SORT_BLOCK tracklets per key; k_sort_work<true> writes
+// perm, ranking the elements of one key in index order, from the position of
+// its block's first element of each key.  DIRECT (up to SORT_DIRECT blocks per
+// group, by capacity): the counts are bins[block * 256 + key'], key' = 255 - key,
+// and each block adds up its group's itself.  Beyond that they are
+// bins[(g * 256 + key') * npg + block in group] (npg blocks per group) and an
+// exclusive scan of bins in place, between the steps, leaves the positions (a sort
+// on a central collision took 23 us in five launches, 19 in four, 10 with DIRECT;
+// a 2 ms slice is as fast either way, which is where the line is drawn).
+// Tracklets of equal estimate keep their order (unit, row, time), so neighbouring
+// tracks share a wave.  Wave w of a workgroup takes the elements
 // [256 w, 256 w + 256) of its block.  Launch at least
-// ceil(capacity / SORT_BLOCK) + ngrp - 1 workgroups, over as many times 256
-// bins.
+// ceil(capacity / SORT_BLOCK) + ngrp - 1 workgroups, over as many times 256 bins.
+#define SORT_DIRECT 512
 #define SORT_BLOCK 1024
-#define XCD_GROUPS 8  // sort groups of the following: one per XCD
 __device__ __forceinline__ uint32_t sort_blocks_per_group(uint32_t n, uint32_t ngrp) {
   return ((n + SORT_BLOCK - 1) / SORT_BLOCK + ngrp - 1) / ngrp;
+}
+
+// Where group g of the sorted order of n items starts (n for g = ngrp).
+__device__ __forceinline__ uint32_t sort_group_start(uint32_t n, uint32_t ngrp, uint32_t g) {
+  const uint64_t s = (uint64_t)g * sort_blocks_per_group(n, ngrp) * SORT_BLOCK;
+  return s < n ? (uint32_t)s : n;
 }
 
 // One item per thread over the sorted order of n items in ngrp groups:
 // workgroup b takes group b % ngrp (gridDim.x is a multiple of ngrp), in the
 // group's order; [i0, i1) with stride di are this thread's positions.
-__device__ __forceinline__ void sorted_items(const uint32_t* __restrict__ bins, uint32_t ngrp,
-                                             uint32_t n, uint32_t& i0, uint32_t& i1,
+__device__ __forceinline__ void sorted_items(uint32_t ngrp, uint32_t n, uint32_t& i0, uint32_t& i1,
                                              uint32_t& di) {
   const uint32_t g = blockIdx.x % ngrp, j = blockIdx.x / ngrp, per = gridDim.x / ngrp;
-  const uint32_t npg = sort_blocks_per_group(n, ngrp);
-  const size_t gsz = (size_t)256 * npg;
-  const uint32_t gs = npg ? bins[g * gsz] : 0u;
-  i1 = npg == 0 ? 0u : g + 1 < ngrp ? bins[(g + 1) * gsz] : n;
-  i0 = j < per ? gs + j * blockDim.x + threadIdx.x : i1;
+  i1 = sort_group_start(n, ngrp, g + 1);
+  i0 = j < per ? sort_group_start(n, ngrp, g) + j * blockDim.x + threadIdx.x : i1;
   di = per * blockDim.x;
 }
 
-template <bool SCATTER>
+template <bool SCATTER, bool DIRECT>
 __global__ __launch_bounds__(256) void k_sort_work(const uint8_t* __restrict__ key,
                                                    const uint32_t* n_tl_dev, uint32_t tl_cap,
                                                    uint32_t ngrp, uint32_t* __restrict__ bins,
@@ -553,12 +566,26 @@ __global__ __launch_bounds__(256) void k_sort_work(const uint8_t* __restrict__ k
   __syncthreads();
   const uint32_t k = threadIdx.x;
   const uint32_t c0 = h[0][k], c1 = h[1][k], c2 = h[2][k], c3 = h[3][k];
-  const size_t bi = (size_t)(grp * 256u + k) * npg + lb;
+  const size_t bi = DIRECT ? (size_t)blockIdx.x * 256u + k : (size_t)(grp * 256u + k) * npg + lb;
   if (!SCATTER) {
     bins[bi] = c0 + c1 + c2 + c3;
     return;
   }
-  const uint32_t base = bins[bi];
+  uint32_t base;
+  if (DIRECT) {
+    // this key's counts in the group and in its blocks before this one
+    __shared__ uint32_t lds[256 / 64 + 1];
+    uint32_t all = 0, before = 0, total;
+#pragma unroll 8
+    for (uint32_t l = 0; l < npg; ++l) {
+      const uint32_t v = bins[(size_t)(grp * npg + l) * 256u + k];
+      all += v;
+      before += l < lb ? v : 0u;
+    }
+    base = sort_group_start(n, ngrp, grp) + block_excl_scan<uint32_t, 256>(all, lds, total) + before;
+  } else {
+    base = bins[bi];
+  }
   __syncthreads();
   h[0][k] = base;
   h[1][k] = base + c0;
@@ -827,8 +854,7 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
                                                const uint32_t* __restrict__ tl_start,
                                                const uint16_t* __restrict__ tl_len,
                                                const uint32_t* __restrict__ pts,
-                                               const uint32_t* __restrict__ perm,
-                                               const uint32_t* __restrict__ bins, uint32_t ngrp,
+                                               const uint32_t* __restrict__ perm, uint32_t ngrp,
                                                uint8_t* __restrict__ key,
                                                const uint32_t* n_tl_dev, uint32_t tl_cap,
                                                FollowOut fo, ulonglong4* __restrict__ work,
@@ -846,7 +872,7 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
   const float chi2max = pv.chi2_max();
   uint32_t w_steps = 0, w_cands = 0, w_upds = 0;
   uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, i1 = n_tl, di = gridDim.x * blockDim.x;
-  if (PASS != FP_AB) sorted_items(bins, ngrp, n_tl, i0, i1, di);
+  if (PASS != FP_AB) sorted_items(ngrp, n_tl, i0, i1, di);
   for (uint32_t i = i0; i < i1; i += di) {
     const uint32_t t = PASS == FP_AB ? i : perm[i];
     FollowLane f;
@@ -933,8 +959,7 @@ __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* 
                                                  const uint32_t* __restrict__ tl_start,
                                                  const uint16_t* __restrict__ tl_len,
                                                  const uint32_t* __restrict__ pts,
-                                                 const uint32_t* __restrict__ perm,
-                                                 const uint32_t* __restrict__ bins, uint32_t ngrp,
+                                                 const uint32_t* __restrict__ perm, uint32_t ngrp,
                                                  uint32_t* __restrict__ qnext,
                                                  uint32_t refill,
                                                  uint8_t* __restrict__ key,
@@ -950,10 +975,7 @@ __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* 
   const uint32_t n_tl = scan_count(n_tl_dev, tl_cap);
   // this workgroup's sort group: positions [gs, ge) of perm
   const uint32_t g = blockIdx.x % ngrp;
-  const uint32_t npg = sort_blocks_per_group(n_tl, ngrp);
-  const size_t gsz = (size_t)256 * npg;
-  const uint32_t gs = npg ? bins[g * gsz] : 0u;
-  const uint32_t ge = npg == 0 ? 0u : g + 1 < ngrp ? bins[(g + 1) * gsz] : n_tl;
+  const uint32_t gs = sort_group_start(n_tl, ngrp, g), ge = sort_group_start(n_tl, ngrp, g + 1);
   // few tracklets: slots per wave and lanes per slot of the group's spread
   const uint32_t wpb = B / 64, gw = gridDim.x / ngrp * wpb;
   const uint32_t j0 = blockIdx.x / ngrp * wpb;
@@ -1479,8 +1501,7 @@ __device__ int refit_seed(uint32_t t, const ClusterView& cl, int32_t anchor, con
 __global__ __launch_bounds__(64) void k_refit(ClusterView cl, const uint32_t* __restrict__ tl_start,
                                               FollowOut fo, const uint32_t* n_tl_dev,
                                               uint32_t tl_cap, const uint16_t* __restrict__ nkept,
-                                              const uint32_t* __restrict__ perm,
-                                              const uint32_t* __restrict__ bins, uint32_t ngrp,
+                                              const uint32_t* __restrict__ perm, uint32_t ngrp,
                                               RefitOut ro,
                                               const DevParams* __restrict__ Pg, DevStatus* st) {
   if (failed(st)) return;
@@ -1488,7 +1509,7 @@ __global__ __launch_bounds__(64) void k_refit(ClusterView cl, const uint32_t* __
   const DevParams* P = params_to_lds(Pg, &Ps);
   const uint32_t n_tl = scan_count(n_tl_dev, tl_cap);
   uint32_t j0, j1, dj;
-  sorted_items(bins, ngrp, n_tl, j0, j1, dj);
+  sorted_items(ngrp, n_tl, j0, j1, dj);
   for (uint32_t j = j0; j < j1; j += dj) {
     const uint32_t t = perm[j];
     ro.flags[t] = 0;
@@ -1527,7 +1548,11 @@ __global__ __launch_bounds__(64) void k_refit(ClusterView cl, const uint32_t* __
         continue;
       }
     }
-    // the whole refit again in FP64 (an FP32 result is discarded)
+    // the whole refit again in FP64 (an FP32 result is discarded), counted for
+    // the status: one atomic for the lanes that get here together
+    const uint64_t redo = __ballot(true);
+    if ((threadIdx.x & 63) == (uint32_t)__builtin_ctzll(redo))
+      atomicAdd(&st->n_fp64_redo, (uint32_t)__popcll(redo));
     double p[5];
     UDCov<double> c;
     double c2 = 0;
@@ -1552,12 +1577,6 @@ __global__ __launch_bounds__(64) void k_refit(ClusterView cl, const uint32_t* __
     ro.flags[t] = TF_TO_FP64 | TF_FP64;
   }
 }
-
-// The tracks refit in FP64 (counted for the status).
-struct GetToFp64 {
-  const uint8_t* flags;
-  __device__ uint32_t operator()(uint32_t t) const { return (flags[t] & TF_TO_FP64) ? 1u : 0u; }
-};
 
 // final keep flag of a tracklet slot
 __device__ __forceinline__ bool final_kept(const uint16_t* nkept, const RefitOut& ro, uint32_t t) {
@@ -1597,40 +1616,43 @@ struct TrackOut {
   int32_t* cluster_track;
 };
 
-__global__ void k_track_totals(const unsigned long long* total, TrackOut to, uint32_t* n_tracks,
-                               uint32_t* n_hits, DevStatus* st) {
-  // after a latched error the scan that wrote *total did not run
-  if (failed(st)) return;
-  const unsigned long long v = *total;
-  const uint32_t nt = (uint32_t)(v >> 32), nh = (uint32_t)v;
-  st->n_tracks = nt;
-  st->n_hits = nh;
-  st->n_fallback = st->n_fp64_redo;
-  if (n_tracks) *n_tracks = nt;
-  if (n_hits) *n_hits = nh;
-  if (nt > to.capacity) latch_capacity(st, OVF_TRACKS, nt);
-  if (nh > to.hit_capacity) latch_capacity(st, OVF_HITS, nh);
-  if (nt <= to.capacity) to.hit_start[nt] = nh;
-}
+struct FinTracks {
+  TrackOut to;
+  uint32_t *n_tracks, *n_hits;
+  DevStatus* st;
+  __device__ void operator()(unsigned long long v) const {
+    const uint32_t nt = (uint32_t)(v >> 32), nh = (uint32_t)v;
+    st->n_tracks = nt;
+    st->n_hits = nh;
+    st->n_fallback = st->n_fp64_redo;
+    if (n_tracks) *n_tracks = nt;
+    if (n_hits) *n_hits = nh;
+    if (nt > to.capacity) latch_capacity(st, OVF_TRACKS, nt);
+    if (nh > to.hit_capacity) latch_capacity(st, OVF_HITS, nh);
+    if (nt <= to.capacity) to.hit_start[nt] = nh;
+  }
+};
 
-// One wave per 64 consecutive tracks (the tracklets that became tracks,
-// listed in order), so that every output array is written in contiguous
-// runs: lane i writes the fields of track j0 + i, the wave writes the
-// parameters and covariances of its tracks as one run each, then the kept hits
-// of all its tracks (one output run, in track order, each track's hits in
-// ascending row order), lane e taking element e of the run: its track is the
-// last one whose first hit is at or before e.
-__global__ __launch_bounds__(256) void k_track_emit(
+// A wave per run of consecutive tracks (the tracklets that became tracks,
+// listed in order; up to 64, fewer where that gives every wave of the nw some),
+// so that every output array is written in contiguous runs: lane i writes the
+// fields of track j0 + i, the wave writes the parameters and covariances of its
+// tracks as one run each, then the kept hits of all its tracks (one output run,
+// in track order, each track's hits in ascending row order), lane e taking
+// element e of the run: its track is the last one whose first hit is at or
+// before e.  Bound by its chains of dependent loads: on a central collision 47 us
+// with 64 tracks per wave, 10 spread (with the clusters' outputs, 51 before).
+#define EMIT_MIN 4      // tracks per wave at least
+#define EMIT_TRACKS 32  // tracklets per wave of the grid
+__device__ __forceinline__ void track_emit(
     ClusterView cl, const uint32_t* __restrict__ tl_start, FollowOut fo,
     const uint32_t* __restrict__ tlist, const uint16_t* __restrict__ nkept, RefitOut ro,
-    const uint32_t* __restrict__ hit_off, TrackOut to, const DevStatus* st) {
-  if (failed(st)) return;
-  const uint32_t n_trk = min(st->n_tracks, to.capacity);
+    const uint32_t* __restrict__ hit_off, const TrackOut& to, uint32_t n_trk, uint32_t nw) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t nw = gridDim.x * (blockDim.x >> 6);
-  for (uint32_t w = uni(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); w < (n_trk + 63) / 64;
+  const uint32_t per = min(64u, max((uint32_t)EMIT_MIN, (n_trk + nw - 1) / nw));
+  for (uint32_t w = uni(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); w * per < n_trk;
        w += nw) {
-    const uint32_t j0 = w * 64, m = min(64u, n_trk - j0);
+    const uint32_t j0 = w * per, m = min(per, n_trk - j0);
     const uint32_t j = j0 + lane;
     uint32_t t = 0, o = 0, n = 0;
     if (lane < m) {
@@ -1680,13 +1702,11 @@ __global__ __launch_bounds__(256) void k_track_emit(
   }
 }
 
-__global__ void k_cluster_track(const uint32_t* __restrict__ owner,
-                                const uint32_t* __restrict__ trk_index, const uint32_t* n_cl_dev,
-                                uint32_t n_cl_cap, uint32_t tl_cap, int32_t* __restrict__ out,
-                                const DevStatus* st) {
-  if (failed(st)) return;
-  const uint32_t n = scan_count(n_cl_dev, n_cl_cap);
-  for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
+__device__ __forceinline__ void cluster_track(const uint32_t* __restrict__ owner,
+                                              const uint32_t* __restrict__ trk_index, uint32_t n,
+                                              uint32_t tl_cap, int32_t* __restrict__ out,
+                                              uint32_t first, uint32_t stride) {
+  for (uint32_t c = first; c < n; c += stride) {
     const uint32_t key = owner[c];
     int32_t v = -1;
     if (key) {
@@ -1698,6 +1718,23 @@ __global__ void k_cluster_track(const uint32_t* __restrict__ owner,
     }
     out[c] = v;
   }
+}
+
+// The tracks' outputs by the first nwg workgroups, the clusters' by the others.
+__global__ __launch_bounds__(256) void k_track_output(
+    ClusterView cl, const uint32_t* __restrict__ tl_start, FollowOut fo,
+    const uint32_t* __restrict__ tlist, const uint16_t* __restrict__ nkept, RefitOut ro,
+    const uint32_t* __restrict__ hit_off, TrackOut to, uint32_t nwg,
+    const uint32_t* __restrict__ owner, const uint32_t* __restrict__ trk_index, uint32_t tl_cap,
+    const DevStatus* st) {
+  if (failed(st)) return;
+  if (blockIdx.x < nwg)
+    track_emit(cl, tl_start, fo, tlist, nkept, ro, hit_off, to, min(st->n_tracks, to.capacity),
+               nwg * (blockDim.x >> 6));
+  else
+    cluster_track(owner, trk_index, scan_count(cl.n_clusters, cl.capacity), tl_cap,
+                  to.cluster_track, (blockIdx.x - nwg) * blockDim.x + threadIdx.x,
+                  (gridDim.x - nwg) * blockDim.x);
 }
 
 // Per-tracklet following result as full rows (debug output).

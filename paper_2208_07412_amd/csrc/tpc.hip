@@ -65,7 +65,6 @@ struct tpc_ctx {
   uint32_t* cl_list = nullptr;  // chunks the streaming peak pass handed back
   ClusterRec* crec = nullptr;  // raw cluster records, indexed like the samples
   void* bsum = nullptr;       // scan block sums (u64)
-  unsigned long long* tot64 = nullptr;
   uint32_t* tot32 = nullptr;
   uint16_t* chain_len = nullptr;  // per listed chain start
   uint32_t* cand = nullptr;       // chain starts, ascending
@@ -98,7 +97,7 @@ struct tpc_ctx {
   uint32_t* cm_info = nullptr;                // compression: sizes of the stream
   // merging: per-segment ends, cells, union-find, member sort
   uint32_t *mg_fs = nullptr, *mg_cell = nullptr, *mg_cnt = nullptr, *mg_off = nullptr,
-           *mg_cur = nullptr, *mg_ends = nullptr, *mg_parent = nullptr, *mg_key = nullptr,
+           *mg_cur = nullptr, *mg_parent = nullptr, *mg_key = nullptr,
            *mg_idx = nullptr, *mg_skey = nullptr, *mg_sidx = nullptr;
   uint8_t* mg_sector = nullptr;
   double *mg_C = nullptr, *mg_tgl = nullptr, *mg_e = nullptr, *mg_cs18 = nullptr;
@@ -130,9 +129,9 @@ struct Layout {
 };
 
 struct Plan {
-  size_t zblk, cblk, win, cl_list, crec, bsum, tot64, tot32, chain_len, cand, start_flag, f_hits, f_state, f_nhits, f_range, f_ok, f_pts, f_key, f_perm, f_bins, f_krow, f_work, f_qnext, pos,
+  size_t zblk, cblk, win, cl_list, crec, bsum, tot32, chain_len, cand, start_flag, f_hits, f_state, f_nhits, f_range, f_ok, f_pts, f_key, f_perm, f_bins, f_krow, f_work, f_qnext, pos,
       owner, nkept, r_par, r_cov, r_chi2, r_row, r_flags, trk_index, qc_part, zp_off, cm_a, cm_b, cm_res, cm_tot, cm_info, mg_fs,
-      mg_cell, mg_cnt, mg_off, mg_cur, mg_ends, mg_parent, mg_key, mg_idx, mg_skey, mg_sidx,
+      mg_cell, mg_cnt, mg_off, mg_cur, mg_parent, mg_key, mg_idx, mg_skey, mg_sidx,
       mg_sector, mg_C, mg_tgl, mg_e, mg_cs18, mg_pos, mg_dir, mg_hxy, hit_off, par, st, total;
   size_t bsum_cap;
   uint32_t nblk, nblk_s, nwin;
@@ -179,8 +178,7 @@ Plan plan_for(const tpc_sizes& m) {
   p.cl_list = L.add<uint32_t>(1 + nur * (p.nwin / 4 + 1));  // chunks handed back
   p.crec = L.add<ClusterRec>(m.max_samples > 0 ? m.max_samples : 1);
   p.bsum = L.add<unsigned long long>(p.bsum_cap);
-  p.tot64 = L.add<unsigned long long>(1);
-  p.tot32 = L.add<uint32_t>(2);
+  p.tot32 = L.add<uint32_t>(1);
   p.chain_len = L.add<uint16_t>(mc / 2 + 1);
   p.cand = L.add<uint32_t>(mc / 2 + 1);
   p.start_flag = L.add<uint8_t>(mc);
@@ -218,7 +216,6 @@ Plan plan_for(const tpc_sizes& m) {
   p.mg_cnt = L.add<uint32_t>(mg_cells(m));
   p.mg_off = L.add<uint32_t>(mg_cells(m) + 1);
   p.mg_cur = L.add<uint32_t>(mg_cells(m) + 1);
-  p.mg_ends = L.add<uint32_t>(2 * mt);
   p.mg_parent = L.add<uint32_t>(mt);
   p.mg_key = L.add<uint32_t>(mt);
   p.mg_idx = L.add<uint32_t>(mt);
@@ -335,25 +332,24 @@ struct StageTimer {
   }
 };
 
-template <typename T, class Get, class Emit>
-void run_scan(tpc_ctx* c, Get get, Emit emit, const uint32_t* n_dev, uint32_t n_cap, T* total,
-              uint32_t* total32) {
-  uint32_t nb = ceil_div(n_cap, SCAN_TILE);
-  if (nb < 1) nb = 1;
+// The exclusive scan of get(i) over the elements: emit(i, prefix, value) for each
+// and fin(total), in one to three launches.
+template <typename T, class Get, class Emit, class Fin>
+void run_scan(tpc_ctx* c, Get get, Emit emit, Fin fin, const uint32_t* n_dev, uint32_t n_cap) {
+  hipStream_t s = c->stream;
+  if (n_cap <= SCAN_ONE) {
+    k_scan_one<T><<<1, 1024, 0, s>>>(get, emit, fin, n_dev, n_cap, c->d_st);
+    return;
+  }
+  const uint32_t nb = ceil_div(n_cap, SCAN_TILE);
   T* bs = reinterpret_cast<T*>(c->bsum);
-  k_scan_reduce<T, Get><<<nb, SCAN_BLOCK, 0, c->stream>>>(get, n_dev, n_cap, bs, c->d_st);
-  k_scan_blocks<T><<<1, 1024, 0, c->stream>>>(bs, nb, total, total32, c->d_st);
-  k_scan_down<T, Get, Emit><<<nb, SCAN_BLOCK, 0, c->stream>>>(get, emit, n_dev, n_cap, bs, c->d_st);
-}
-
-// The total alone (the reduce half of run_scan).
-template <typename T, typename Get>
-void run_count(tpc_ctx* c, Get get, const uint32_t* n_dev, uint32_t n_cap, uint32_t* total32) {
-  uint32_t nb = ceil_div(n_cap, SCAN_TILE);
-  if (nb < 1) nb = 1;
-  T* bs = reinterpret_cast<T*>(c->bsum);
-  k_scan_reduce<T, Get><<<nb, SCAN_BLOCK, 0, c->stream>>>(get, n_dev, n_cap, bs, c->d_st);
-  k_scan_blocks<T><<<1, 1024, 0, c->stream>>>(bs, nb, (T*)nullptr, total32, c->d_st);
+  k_scan_reduce<T><<<nb, SCAN_BLOCK, 0, s>>>(get, n_dev, n_cap, bs, c->d_st);
+  if (nb <= SCAN_SELF) {
+    k_scan_down<true, T><<<nb, SCAN_BLOCK, 0, s>>>(get, emit, fin, n_dev, n_cap, bs);
+  } else {
+    k_scan_blocks<T><<<1, 1024, 0, s>>>(bs, nb, c->d_st);
+    k_scan_down<false, T><<<nb, SCAN_BLOCK, 0, s>>>(get, emit, fin, n_dev, n_cap, bs);
+  }
 }
 
 struct GetU32 {
@@ -487,10 +483,8 @@ void launch_cluster(tpc_ctx* c, const ZsArgs& za, uint32_t nblk_s, uint32_t n_ur
   }
   {
     StageTimer tm(c, 2);
-    run_scan<uint32_t>(c, GetU32{c->win}, EmitU32{c->win}, nullptr, nwt, (uint32_t*)nullptr,
-                       n_clusters);
-    k_crow_start<<<grid_for(n_ur + 1, 256), 256, 0, s>>>(c->win, nwin, n_ur, n_clusters, capacity,
-                                                         crow_start, c->d_st);
+    run_scan<uint32_t>(c, GetU32{c->win}, EmitWindow{c->win, crow_start, nwin},
+                       FinClusters{crow_start + n_ur, n_clusters, capacity, c->d_st}, nullptr, nwt);
   }
   {
     StageTimer tm(c, 3);
@@ -506,11 +500,9 @@ int stage_cluster(tpc_ctx* c, const tpc_zs_input* in, tpc_clusters* out) {
   hipStream_t s = c->stream;
   {
     StageTimer tm(c, 0);
-    k_block_index<false><<<n_ur * BI_PARTS, 256, 0, s>>>(in->time, in->pad, in->adc, in->row_start,
-                                                         n_ur,
-                                              nblk_s,
-                                              CL_BSHIFT, in->n_time_bins, in->n_samples, c->zblk,
-                                              c->d_par, c->d_st, 1);
+    k_sample_index<<<n_ur * BI_PARTS, 256, 0, s>>>(in->time, in->pad, in->adc, in->row_start, n_ur,
+                                                   nblk_s, in->n_time_bins, in->n_samples, c->zblk,
+                                                   c->d_par, c->d_st);
   }
   ClusterOut co{out->capacity, out->y_fx, out->z_fx, out->dpad, out->dtime, out->s2pad, out->s2time,
                 out->qtot, out->qmax, out->ppad, out->ptime, out->flags, out->sp, out->st,
@@ -548,13 +540,9 @@ int stage_grid(tpc_ctx* c, const tpc_clusters* cl) {
   const uint32_t n_ur = cl->n_units * NROW;
   const uint32_t nblk = ceil_div(cl->n_time_bins, 1u << CG_BSHIFT);
   StageTimer tm(c, 4);
-  k_block_index<true><<<n_ur, 256, 0, c->stream>>>(cl->ptime, cl->ppad, nullptr, cl->crow_start,
-                                                   n_ur, nblk,
-                                             CG_BSHIFT,
-                                             cl->n_time_bins, cl->capacity, c->cblk, c->d_par,
-                                             c->d_st, 0);
-  k_pack_pos<<<grid_for(cl->capacity, 256, kCapStream), 256, 0, c->stream>>>(cl->y_fx, cl->z_fx, cl->n_clusters,
-                                                                 cl->capacity, c->pos, c->d_st);
+  k_hit_grid<<<n_ur + grid_for(cl->capacity, 256, kCapStream), 256, 0, c->stream>>>(
+      cluster_view(c, cl), cl->ppad, n_ur, nblk, cl->n_time_bins, c->cblk, cl->y_fx, cl->z_fx,
+      c->pos, c->owner, c->d_par, c->d_st);
   return launch_ok();
 }
 
@@ -577,14 +565,13 @@ int stage_tracklets(tpc_ctx* c, const tpc_clusters* cl, tpc_links* l, tpc_trackl
   // chain starts (at most one per two clusters: chains are disjoint and have
   // at least two), their chain lengths, then the tracklets in start order
   const uint32_t capc = cap / 2 + 1;
-  run_scan<uint32_t>(c, GetStart{c->start_flag}, EmitStart{c->cand, capc}, cl->n_clusters, cap,
-                     (uint32_t*)nullptr, c->tot32);
+  run_scan<uint32_t>(c, GetStart{c->start_flag}, EmitStart{c->cand, capc},
+                     StoreFin<uint32_t>{c->tot32}, cl->n_clusters, cap);
   k_chain_len<<<grid_for(capc, 256, kCapStream), 256, 0, s>>>(c->cand, c->tot32, capc, l->upc, cl->n_clusters,
                                                   cap, c->chain_len, c->d_par, c->d_st);
   run_scan<uint32_t>(c, GetKeepLen{c->chain_len},
-                     EmitTracklet{c->cand, c->chain_len, t->start, t->len, t->capacity}, c->tot32,
-                     capc, (uint32_t*)nullptr, c->tot32 + 1);
-  k_tracklet_count<<<1, 1, 0, s>>>(c->tot32 + 1, t->capacity, t->n_tracklets, c->d_st);
+                     EmitTracklet{c->cand, c->chain_len, t->start, t->len, t->capacity},
+                     FinTracklets{t->capacity, t->n_tracklets, c->d_st}, c->tot32, capc);
   return launch_ok();
 }
 
@@ -605,20 +592,26 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
   // ngrp groups sorted each on its own (the following: one group per XCD)
   auto sort_by_key = [&](uint32_t ngrp) {
     const uint32_t nb = nsb + ngrp - 1;
-    k_sort_work<false><<<nb, 256, 0, s>>>(c->f_key, t->n_tracklets, tcap, ngrp, c->f_bins,
-                                          c->f_perm, c->d_st);
-    run_scan<uint32_t>(c, GetU32{c->f_bins}, EmitU32{c->f_bins}, (const uint32_t*)nullptr,
-                       256 * nb, (uint32_t*)nullptr, (uint32_t*)nullptr);
-    k_sort_work<true><<<nb, 256, 0, s>>>(c->f_key, t->n_tracklets, tcap, ngrp, c->f_bins,
-                                         c->f_perm, c->d_st);
+    auto step = [&](auto scatter, auto direct) {
+      k_sort_work<decltype(scatter)::value, decltype(direct)::value><<<nb, 256, 0, s>>>(
+          c->f_key, t->n_tracklets, tcap, ngrp, c->f_bins, c->f_perm, c->d_st);
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    if (ceil_div(nsb, ngrp) <= SORT_DIRECT) {
+      step(No{}, Yes{});
+      step(Yes{}, Yes{});
+    } else {
+      step(No{}, No{});
+      run_scan<uint32_t>(c, GetU32{c->f_bins}, EmitU32{c->f_bins}, NoFin{}, nullptr, 256 * nb);
+      step(Yes{}, No{});
+    }
   };
-  // per-call counters of the fit stage
-  k_fill<uint32_t><<<1, 64, 0, s>>>(&c->d_st->n_fallback, 0u, 5);
   {
     StageTimer tm(c, 6);  // the tracklets' seed points belong to tracklet building
     k_tracklet_points<<<grid_for(tcap, 256, kCapStream), 256, 0, s>>>(cv, n_ur, l->upc, t->start, t->len,
                                                            t->n_tracklets, tcap, c->f_pts,
-                                                           c->f_key, c->d_st);
+                                                           c->f_key, c->f_qnext, c->d_st);
   }
   {
     StageTimer tm(c, 7);
@@ -633,7 +626,6 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
       if (c->tune.follow_mode == 2) {
         // lane refill: a grid of the resident workgroups (a multiple of ng),
         // each pass over the tracklets sorted by the most rows it can take
-        k_fill<uint32_t><<<1, 64, 0, s>>>(c->f_qnext, 0u, 2 * ng);
         // waves beyond the resident grid leave their work counters untouched
         if (Cv)
           k_fill<unsigned long long><<<grid_for(8 * nwf, 256), 256, 0, s>>>(
@@ -664,11 +656,11 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
         const uint32_t refill = FOLLOW_REFILL;
         sort_by_key(ng);
         k_follow_q<Bv, FP_A, Cv><<<grid_q(occ_a), Bv, 0, s>>>(
-            cv, c->cblk, nblk, l->upc, t->start, t->len, c->f_pts, c->f_perm, c->f_bins, ng,
+            cv, c->cblk, nblk, l->upc, t->start, t->len, c->f_pts, c->f_perm, ng,
             c->f_qnext, refill, c->f_key, t->n_tracklets, tcap, fo, c->f_work, c->d_par, c->d_st);
         sort_by_key(ng);
         k_follow_q<Bv, FP_B, Cv><<<grid_q(occ_b), Bv, 0, s>>>(
-            cv, c->cblk, nblk, l->upc, t->start, t->len, c->f_pts, c->f_perm, c->f_bins, ng,
+            cv, c->cblk, nblk, l->upc, t->start, t->len, c->f_pts, c->f_perm, ng,
             c->f_qnext + ng, refill, c->f_key, t->n_tracklets, tcap, fo, c->f_work + nwf, c->d_par,
             c->d_st);
         return;
@@ -680,18 +672,18 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
           sort_by_key(ng);
           if (pass == 0)
             k_follow<Bv, FP_A, Cv><<<gf, Bv, 0, s>>>(cv, c->cblk, nblk, l->upc, t->start, t->len,
-                                                     c->f_pts, c->f_perm, c->f_bins, ng, c->f_key,
+                                                     c->f_pts, c->f_perm, ng, c->f_key,
                                                      t->n_tracklets, tcap, fo, c->f_work, c->d_par,
                                                      c->d_st);
           else
             k_follow<Bv, FP_B, Cv><<<gf, Bv, 0, s>>>(cv, c->cblk, nblk, l->upc, t->start, t->len,
-                                                     c->f_pts, c->f_perm, c->f_bins, ng, c->f_key,
+                                                     c->f_pts, c->f_perm, ng, c->f_key,
                                                      t->n_tracklets, tcap, fo, c->f_work + nwf,
                                                      c->d_par, c->d_st);
         }
       } else {
         k_follow<Bv, FP_AB, Cv><<<gf, Bv, 0, s>>>(cv, c->cblk, nblk, l->upc, t->start, t->len,
-                                                  c->f_pts, nullptr, nullptr, 1u, c->f_key,
+                                                  c->f_pts, nullptr, 1u, c->f_key,
                                                   t->n_tracklets, tcap, fo, c->f_work, c->d_par,
                                                   c->d_st);
       }
@@ -709,8 +701,6 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
   }
   {
     StageTimer tm(c, 8);
-    k_fill_dev<uint32_t><<<grid_for(ccap, 256, kCapStream), 256, 0, s>>>(c->owner, 0u,
-                                                                        cl->n_clusters, ccap);
     // one wave per tracklet, about 8 tracklets per wave
     k_claim<false><<<gw, 256, 0, s>>>(fo, t->n_tracklets, tcap, c->owner, ccap, c->d_par, c->d_st);
     k_claim<true><<<gw, 256, 0, s>>>(fo, t->n_tracklets, tcap, c->owner, ccap, c->d_par, c->d_st);
@@ -728,26 +718,22 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
     const int rw = c->tune.refit_waves;
     const size_t lds_pad = rw ? (size_t)(160 << 10) / rw - sizeof(DevParams) - 256 : 0;
     k_refit<<<ceil_div(g64, ng) * ng, 64, lds_pad, s>>>(cv, t->start, fo, t->n_tracklets, tcap,
-                                                        c->nkept, c->f_perm, c->f_bins, ng, ro,
+                                                        c->nkept, c->f_perm, ng, ro,
                                                         c->d_par, c->d_st);
   }
-  {
-    StageTimer tm(c, 10);
-    // the tracks the refit redid in FP64, counted for the status (a reduction,
-    // not one same-address atomic per track)
-    run_count<uint32_t>(c, GetToFp64{ro.flags}, t->n_tracklets, tcap, &c->d_st->n_fp64_redo);
-  }
+  { StageTimer tm(c, 10); }  // no launch of its own: the refit counts the tracks it redid in FP64
   StageTimer tm(c, 11);
-  run_scan<unsigned long long>(c, GetTrackPair{c->nkept, ro}, EmitTrackPair{c->trk_index, c->hit_off, c->f_perm, tcap},
-                               t->n_tracklets, tcap, c->tot64, (uint32_t*)nullptr);
   TrackOut to{tr->capacity, tr->hit_capacity, tr->tracklet, tr->par, tr->cov, tr->chi2, tr->ndf,
               tr->row, tr->flags, tr->z_anchor, tr->hit_start, tr->hits, tr->cluster_track};
-  k_track_totals<<<1, 1, 0, s>>>(c->tot64, to, tr->n_tracks, tr->n_hits, c->d_st);
   // tracklets of the tracks listed in f_perm (free after the refit)
-  k_track_emit<<<grid_for(tcap, 256, kCapStream), 256, 0, s>>>(cv, t->start, fo, c->f_perm, c->nkept, ro,
-                                                    c->hit_off, to, c->d_st);
-  k_cluster_track<<<grid_for(ccap, 256, kCapStream), 256, 0, s>>>(c->owner, c->trk_index, cl->n_clusters, ccap,
-                                                      tcap, tr->cluster_track, c->d_st);
+  run_scan<unsigned long long>(c, GetTrackPair{c->nkept, ro},
+                               EmitTrackPair{c->trk_index, c->hit_off, c->f_perm, tcap},
+                               FinTracks{to, tr->n_tracks, tr->n_hits, c->d_st}, t->n_tracklets,
+                               tcap);
+  const uint32_t ge = grid_for(tcap, EMIT_TRACKS * 4, kCapStream);
+  k_track_output<<<ge + grid_for(ccap, 256, kCapStream), 256, 0, s>>>(
+      cv, t->start, fo, c->f_perm, c->nkept, ro, c->hit_off, to, ge, c->owner, c->trk_index, tcap,
+      c->d_st);
   if (tr->follow_hits)
     k_follow_export<<<grid_for((uint64_t)tcap * NROW, 256), 256, 0, s>>>(fo, t->n_tracklets, tcap,
                                                                           tr->follow_hits, c->d_st);
@@ -852,7 +838,6 @@ int tpc_create(tpc_ctx** out, const tpc_params* p, const tpc_sizes* max, void* h
   c->cl_list = (uint32_t*)(base + pl.cl_list);
   c->crec = (ClusterRec*)(base + pl.crec);
   c->bsum = base + pl.bsum;
-  c->tot64 = (unsigned long long*)(base + pl.tot64);
   c->tot32 = (uint32_t*)(base + pl.tot32);
   c->chain_len = (uint16_t*)(base + pl.chain_len);
   c->cand = (uint32_t*)(base + pl.cand);
@@ -891,7 +876,6 @@ int tpc_create(tpc_ctx** out, const tpc_params* p, const tpc_sizes* max, void* h
   c->mg_cnt = (uint32_t*)(base + pl.mg_cnt);
   c->mg_off = (uint32_t*)(base + pl.mg_off);
   c->mg_cur = (uint32_t*)(base + pl.mg_cur);
-  c->mg_ends = (uint32_t*)(base + pl.mg_ends);
   c->mg_parent = (uint32_t*)(base + pl.mg_parent);
   c->mg_key = (uint32_t*)(base + pl.mg_key);
   c->mg_idx = (uint32_t*)(base + pl.mg_idx);
@@ -957,8 +941,8 @@ int tpc_decode_zs_pages(tpc_ctx* c, const uint32_t* pages, uint32_t n_pages, tpc
     k_fill<uint32_t><<<1, 64, 0, s>>>(out->n_samples, 0u, 1);
     return launch_ok();
   }
-  run_scan<uint32_t>(c, GetPageSamples{pages, out->n_units}, EmitPageOffset{c->zp_off}, nullptr,
-                     n_pages, (uint32_t*)nullptr, c->tot32);
+  run_scan<uint32_t>(c, GetPageSamples{pages, out->n_units}, EmitPageOffset{c->zp_off},
+                     StoreFin<uint32_t>{c->tot32}, nullptr, n_pages);
   // pages per workgroup in turn (a 2 ms Pb-Pb slice's 86,836 pages: 1.18 ms
   // with 4096 workgroups, 1.11 with 16384, 1.13 with one per page)
   const uint32_t g = n_pages < 16384 ? n_pages : 16384;
@@ -998,11 +982,12 @@ int tpc_compress(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, tpc_c
       cv, tv, b30, c->d_par, c->cm_a, c->f_range, out->res_hist, c->cm_res, res_cap, c->d_st);
   k_cm_row_bits<<<n_ur, 256, 0, s>>>(cv, tr->cluster_track, c->cm_b, c->d_st);
   run_scan<unsigned long long>(c, CmGetU32{c->cm_a}, CmEmitTrack{out->stream, out->capacity},
-                               tr->n_tracks, tr->capacity, c->cm_tot, (uint32_t*)nullptr);
+                               StoreFin<unsigned long long>{c->cm_tot}, tr->n_tracks,
+                               tr->capacity);
   run_scan<unsigned long long>(
       c, CmGetU32{c->cm_b},
-      CmEmitRow{out->stream, out->capacity, tr->n_tracks, tr->capacity, c->cm_tot}, nullptr, n_ur,
-      c->cm_tot + 1, (uint32_t*)nullptr);
+      CmEmitRow{out->stream, out->capacity, tr->n_tracks, tr->capacity, c->cm_tot},
+      StoreFin<unsigned long long>{c->cm_tot + 1}, nullptr, n_ur);
   k_cm_finish<<<1, 1, 0, s>>>(out->stream, out->capacity, cl->n_units, tr->n_tracks, tr->capacity,
                               tr->hit_start, cl->n_clusters, cl->capacity, c->cm_tot,
                               out->n_words, c->cm_info, c->d_st);
@@ -1027,8 +1012,8 @@ int tpc_decompress(tpc_ctx* c, const uint32_t* stream, uint32_t stream_words,
                                   out->capacity, out->n_clusters, c->cm_info, c->d_st);
   k_cm_dec_counts<<<grid_for(max_rec, 256, 4096), 256, 0, s>>>(stream, c->cm_info, c->cm_a,
                                                                c->d_st);
-  run_scan<unsigned long long>(c, CmGetU32{c->cm_a}, CmEmitOff{c->cm_b}, c->cm_info + 5, max_rec,
-                               c->cm_tot, (uint32_t*)nullptr);
+  run_scan<unsigned long long>(c, CmGetU32{c->cm_a}, CmEmitOff{c->cm_b},
+                               StoreFin<unsigned long long>{c->cm_tot}, c->cm_info + 5, max_rec);
   const CmDecOut o{out->capacity, out->unit, out->row, out->y_fx, out->z_fx,
                    out->qtot, out->qmax, out->flags, out->track};
   // In two steps where the scratch holds a raw record per cluster that the
@@ -1060,6 +1045,13 @@ struct MgEmitOff {
     cur[i] = pre;
   }
 };
+struct MgFinOff {  // the table's closing entry, and the number of ends
+  uint32_t *off_end, *total;
+  __device__ void operator()(uint32_t n) const {
+    *off_end = n;
+    *total = n;
+  }
+};
 
 int tpc_merge_tracks(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, tpc_merged* out) {
   if (!c || check_clusters(c, cl, false) || !tr || !out || !out->n_merged || !out->label ||
@@ -1078,22 +1070,17 @@ int tpc_merge_tracks(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, t
   const uint32_t nzb = mg_nzb(cl->n_time_bins);
   const uint32_t n_cells = ((cl->n_units + 35) / 36) * 2 * MG_NXY * MG_NXY * nzb;
   const MgSegs S{c->mg_fs, c->mg_sector, c->mg_C, c->mg_tgl, c->mg_e};
-  k_fill<uint32_t><<<grid_for(n_cells, 256, 4096), 256, 0, s>>>(c->mg_cnt, 0u, n_cells);
-  k_fill<double><<<grid_for((uint64_t)out->capacity * TPC_MERGE_FIT, 256, 4096), 256, 0, s>>>(
-      out->fit, 0.0, out->capacity * TPC_MERGE_FIT);
-  k_mg_init<<<grid_for(cap, 256, 4096), 256, 0, s>>>(c->mg_parent, out->near_tie, c->mg_idx, cap,
-                                                     c->d_st);
+  k_mg_init<<<grid_for((uint64_t)out->capacity * TPC_MERGE_FIT, 256, 4096), 256, 0, s>>>(
+      c->mg_cnt, n_cells, out->fit, out->capacity * TPC_MERGE_FIT, c->mg_parent, out->near_tie,
+      c->mg_idx, cap, out->n_merged, c->d_st);
   k_mg_segments<<<grid_for(cap, 256, 4096), 256, 0, s>>>(
       cl->crow_start, n_ur, cl->y_fx, cl->z_fx, cl->n_clusters, cl->capacity, tr->par, tr->row,
       tr->hit_start, tr->hits, tr->hit_capacity, tr->n_tracks, cap, c->mg_cs18, c->par.bz_b, nzb,
       S, c->mg_cell, c->mg_cnt, c->d_par, c->d_st);
-  run_scan<uint32_t>(c, GetU32{c->mg_cnt}, MgEmitOff{c->mg_off, c->mg_cur}, nullptr, n_cells,
-                     (uint32_t*)nullptr, c->tot32);
-  k_mg_total<<<1, 1, 0, s>>>(c->mg_off, c->tot32, n_cells, c->d_st);
+  run_scan<uint32_t>(c, GetU32{c->mg_cnt}, MgEmitOff{c->mg_off, c->mg_cur},
+                     MgFinOff{c->mg_off + n_cells, c->tot32}, nullptr, n_cells);
   k_mg_fill_cells<<<grid_for(2 * (uint64_t)cap, 256, 4096), 256, 0, s>>>(
-      c->mg_cell, tr->n_tracks, cap, c->mg_cur, c->mg_ends, c->d_st);
-  k_mg_pack<<<grid_for(2 * (uint64_t)cap, 256, 4096), 256, 0, s>>>(c->mg_ends, c->tot32, S,
-                                                                   c->mg_pos, c->mg_dir, c->d_st);
+      c->mg_cell, tr->n_tracks, cap, c->mg_cur, S, c->mg_pos, c->mg_dir, c->d_st);
   k_mg_pairs<<<grid_for(2 * (uint64_t)cap * MG_RUNS, 256, MG_PAIR_BLOCKS), 256, 0, s>>>(
       S, nzb, c->tot32, c->mg_off, c->mg_cell, c->mg_pos, c->mg_dir, c->mg_parent, out->near_tie,
       c->d_st);
@@ -1102,31 +1089,31 @@ int tpc_merge_tracks(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, t
       tr->hits, hit_bound, tr->n_tracks, cap, c->mg_cs18, c->mg_hxy,
       reinterpret_cast<int32_t*>(c->cm_res), c->d_par, c->d_st);
   k_mg_labels<<<grid_for(cap, 256, 4096), 256, 0, s>>>(c->mg_parent, tr->n_tracks, cap, out->label,
-                                                       c->mg_key, c->d_st);
-  // members grouped by component in ascending index: labels are below 2^24
-  {
-    const uint32_t nb = ceil_div(cap, MG_SORT_BLOCK);
-    uint32_t *ki = c->mg_key, *vi = c->mg_idx, *ko = c->mg_skey, *vo = c->mg_sidx;
-    for (int shift = 0; shift < 24; shift += 8) {
-      k_mg_rsort<false><<<nb, 256, 0, s>>>(ki, vi, tr->n_tracks, cap, shift, c->f_bins, ko, vo,
-                                           c->d_st);
-      run_scan<uint32_t>(c, GetU32{c->f_bins}, EmitU32{c->f_bins}, nullptr, 256 * nb,
-                         (uint32_t*)nullptr, c->tot32 + 1);
-      k_mg_rsort<true><<<nb, 256, 0, s>>>(ki, vi, tr->n_tracks, cap, shift, c->f_bins, ko, vo,
-                                          c->d_st);
-      uint32_t* t = ki;
-      ki = ko;
-      ko = t;
-      t = vi;
-      vi = vo;
-      vo = t;
+                                                       c->mg_key, out->n_merged, c->d_st);
+  // members grouped by component in ascending index (labels are below cap)
+  uint32_t *ki = c->mg_key, *vi = c->mg_idx, *ko = c->mg_skey, *vo = c->mg_sidx;
+  const uint32_t nb = ceil_div(cap, MG_SORT_BLOCK);
+  for (int shift = 0; shift < 32 && (cap - 1) >> shift; shift += 8) {
+    auto step = [&](auto scatter, auto direct) {
+      k_mg_rsort<decltype(scatter)::value, decltype(direct)::value><<<nb, 256, 0, s>>>(
+          ki, vi, tr->n_tracks, cap, shift, c->f_bins, ko, vo, c->d_st);
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    if (nb <= MG_SORT_DIRECT) {
+      step(No{}, Yes{});
+      step(Yes{}, Yes{});
+    } else {
+      step(No{}, No{});
+      run_scan<uint32_t>(c, GetU32{c->f_bins}, EmitU32{c->f_bins}, NoFin{}, nullptr, 256 * nb);
+      step(Yes{}, No{});
     }
-    // three passes: the result is in (mg_skey, mg_sidx)
+    std::swap(ki, ko);
+    std::swap(vi, vo);
   }
   k_mg_fit<<<grid_for(cap, 4, 65536), 64, 0, s>>>(
-      c->mg_skey, c->mg_sidx, tr->n_tracks, cap, tr->hit_start, hit_bound, c->mg_hxy,
+      ki, vi, tr->n_tracks, cap, tr->hit_start, hit_bound, c->mg_hxy,
       reinterpret_cast<const int32_t*>(c->cm_res), out->fit, c->d_st);
-  run_count<uint32_t>(c, MgIsRoot{out->label}, tr->n_tracks, cap, out->n_merged);
   return launch_ok();
 }
 
