@@ -1134,43 +1134,71 @@ __device__ __forceinline__ uint32_t track_key(uint32_t nh, uint32_t t) {
 // of the tracklet's hit table (contiguous), so every table read is coalesced.
 // The tracklet index is made wave-uniform so its scalars load once.
 
-#define KEEP_GROUP 4  // consecutive tracklets per wave of the claim and keep kernels
-
-// Lane k of a wave loads what the claim and keep need of tracklet t0 + k
-// (t0 + k < t1): 1 | hit count << 8 | row range << 16 for a tracklet that bids
-// (followed, at least min_track_hits hits), else 0.  Read back per tracklet
-// with a lane read, so the fields come in one coalesced load per array.
-__device__ __forceinline__ uint32_t bid_info(const FollowOut& fo, uint32_t t0, uint32_t t1,
-                                             int min_hits) {
+// A wave takes KEEP_GROUP consecutive tracklets and the rows of their hit
+// tables one after the other, 64 to a chunk, KEEP_CHUNKS chunks at a time: their
+// hits are loaded together, then the hits' owners.  Bound by the gathers of
+// owners, a line each (on a 2 ms slice the three kernels took 745 us with a
+// tracklet at a time, 64 rows to a load, 668 this way; 741 with 8 tracklets; a
+// tracklet per lane, 64 of them over one row after the other, was slower, 880: the
+// lanes' hits share few lines, and more claims were stored twice).
+#define KEEP_GROUP 4
+#define KEEP_CHUNKS 4
+struct BidGroup {
+  uint32_t info;  // lane k: 1 | hit count << 8 | row range << 16 of tracklet t0 + k if it
+                  // bids (followed, at least min_track_hits hits), else 0
+  uint32_t pre;   // lane k: rows of the tracklets before it
+  uint32_t tot;   // rows of the group
+  uint32_t end[KEEP_GROUP];  // rows up to and with the k-th (uniform)
+};
+__device__ __forceinline__ BidGroup bid_group(const FollowOut& fo, uint32_t t0, uint32_t t1,
+                                              int min_hits) {
+  BidGroup g;
   const uint32_t t = t0 + (threadIdx.x & 63);
-  if (t >= t1 || !fo.ok[t]) return 0u;
-  const uint32_t nh = fo.nhits[t];
-  return (int)nh >= min_hits ? 1u | (nh << 8) | ((uint32_t)fo.range[t] << 16) : 0u;
+  g.info = 0;
+  if (t < t1 && fo.ok[t]) {
+    const uint32_t nh = fo.nhits[t];
+    if ((int)nh >= min_hits) g.info = 1u | (nh << 8) | ((uint32_t)fo.range[t] << 16);
+  }
+  const uint32_t len = g.info ? (g.info >> 24) - ((g.info >> 16) & 255) + 1 : 0u;
+  const uint32_t end = wave_incl_scan(len);
+  g.pre = end - len;
+#pragma unroll
+  for (int k = 0; k < KEEP_GROUP; ++k)
+    g.end[k] = (uint32_t)__builtin_amdgcn_readlane((int)end, k);
+  g.tot = g.end[KEEP_GROUP - 1];
+  return g;
 }
 
-// The hit-table entries of the first 64 rows of each bidding tracklet of a
-// group (lane l: row lo + l, or -1), loaded together so that their latencies
-// overlap instead of coming one tracklet after the other.
-__device__ __forceinline__ void first_rows(const FollowOut& fo, uint32_t t0, uint32_t info,
-                                           int32_t (&first)[KEEP_GROUP]) {
-  const int lane = (int)(threadIdx.x & 63);
+// A row of the group: its tracklet (t0 + k, what bid_group holds of it), the row
+// and the hit there (-1: none, or past the group's rows).
+struct BidRow {
+  uint32_t k, info;
+  int32_t r, c;
+};
+__device__ __forceinline__ BidRow bid_row(const BidGroup& g, const FollowOut& fo, uint32_t t0,
+                                          uint32_t e, uint32_t n_cl_cap) {
+  BidRow x;
+  x.k = 0;
 #pragma unroll
-  for (int kk = 0; kk < KEEP_GROUP; ++kk) {
-    const uint32_t inf = (uint32_t)__builtin_amdgcn_readlane((int)info, kk);
-    const int lo = (inf >> 16) & 255, hi = inf >> 24;
-    const int r = lo + lane;
-    first[kk] = inf && r <= hi ? fo.hits[(size_t)(t0 + kk) * NROW + r] : -1;
-  }
+  for (int k = 0; k + 1 < KEEP_GROUP; ++k) x.k += e >= g.end[k];
+  x.info = (uint32_t)__shfl((int)g.info, (int)x.k);
+  x.r = (int32_t)(((x.info >> 16) & 255) + e - (uint32_t)__shfl((int)g.pre, (int)x.k));
+  x.c = e < g.tot ? fo.hits[(size_t)(t0 + x.k) * NROW + x.r] : -1;
+  if ((uint32_t)x.c >= n_cl_cap) x.c = -1;
+  return x;
 }
 
 // Every followed tracklet with enough hits bids for its clusters: the owner
 // of a cluster is the largest key among its bidders.  Two launches instead of
-// one atomicMax per hit: FIX = false stores every bidder's key (one of them
-// lands); FIX = true reads the owner back and raises it with atomicMax only
-// where the bidder's key is larger.  Owners only grow in the second launch
-// and hold bidders' keys, so the largest bidder either reads its own key or
-// raises the owner to it: the result is the maximum.  Most clusters have one
-// bidder and cost a plain store and a load instead of a device-scope atomic.
+// one atomicMax per hit: FIX = false stores a bidder's key where the owner it
+// reads is smaller (of bidders that read at the same time one lands); FIX = true
+// reads the owner back and raises it with atomicMax only where the bidder's key
+// is larger.  Owners hold bidders' keys and only grow in the second launch, so
+// the largest bidder either reads its own key or raises the owner to it: the
+// result is the maximum.  Most clusters have one bidder and cost a load and a
+// plain store instead of a device-scope atomic, and most of the others have the
+// largest before the second launch (storing without the look: 668 us for claims
+// and keep on a 2 ms slice, with it 578).
 template <bool FIX>
 __global__ __launch_bounds__(256) void k_claim(FollowOut fo, const uint32_t* n_tl_dev,
                                                uint32_t tl_cap,
@@ -1187,26 +1215,24 @@ __global__ __launch_bounds__(256) void k_claim(FollowOut fo, const uint32_t* n_t
     // equal hit counts the one that wins (the lower index) tends to store
     // last (a store order sorted by key wins more clusters at once but loses
     // the locality of neighbouring tracklets and costs more than it saves)
-    const uint32_t g = FIX ? i : n_grp - 1 - i;
-    const uint32_t t0 = g * KEEP_GROUP, t1 = min(t0 + KEEP_GROUP, n_tl);
-    const uint32_t info = bid_info(fo, t0, t1, P->min_track_hits);
-    int32_t first[KEEP_GROUP];
-    first_rows(fo, t0, info, first);
+    const uint32_t t0 = (FIX ? i : n_grp - 1 - i) * KEEP_GROUP, t1 = min(t0 + KEEP_GROUP, n_tl);
+    const BidGroup g = bid_group(fo, t0, t1, P->min_track_hits);
+    const uint32_t nb = (g.tot + 64 * KEEP_CHUNKS - 1) / (64 * KEEP_CHUNKS);
+    for (uint32_t j = 0; j < nb; ++j) {
+      const uint32_t e0 = (FIX ? j : nb - 1 - j) * 64 * KEEP_CHUNKS + lane;
+      BidRow x[KEEP_CHUNKS];
 #pragma unroll
-    for (int k = 0; k < KEEP_GROUP; ++k) {
-      const int kk = FIX ? k : KEEP_GROUP - 1 - k;
-      if (kk >= (int)(t1 - t0)) continue;
-      const uint32_t inf = (uint32_t)__builtin_amdgcn_readlane((int)info, kk);
-      if (!inf) continue;
-      const uint32_t t = t0 + kk;
-      const uint32_t key = track_key((inf >> 8) & 255, t);
-      const int lo = (inf >> 16) & 255, hi = inf >> 24;
-      const int32_t* H = fo.hits + (size_t)t * NROW;
-      for (int r = lo + (int)lane; r <= hi; r += 64) {
-        const int32_t c = r < lo + 64 ? first[kk] : H[r];
-        if (c < 0 || (uint32_t)c >= n_cl_cap) continue;
-        if (!FIX) owner[c] = key;
-        else if (owner[c] < key) atomicMax(&owner[c], key);
+      for (int m = 0; m < KEEP_CHUNKS; ++m) x[m] = bid_row(g, fo, t0, e0 + 64 * m, n_cl_cap);
+      uint32_t o[KEEP_CHUNKS];
+#pragma unroll
+      for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0xFFFFFFFFu;
+#pragma unroll
+      for (int mm = 0; mm < KEEP_CHUNKS; ++mm) {
+        const int m = FIX ? mm : KEEP_CHUNKS - 1 - mm;
+        const uint32_t key = track_key((x[m].info >> 8) & 255, t0 + x[m].k);
+        if (o[m] >= key) continue;
+        if (FIX) atomicMax(&owner[x[m].c], key);
+        else owner[x[m].c] = key;
       }
     }
   }
@@ -1229,38 +1255,35 @@ __global__ __launch_bounds__(256) void k_keep(FollowOut fo, const uint32_t* n_tl
   // a wave takes KEEP_GROUP consecutive tracklets; lane k collects the count
   // of the k-th, and the counts go out as one run per array
   const uint32_t n_grp = (n_tl + KEEP_GROUP - 1) / KEEP_GROUP;
-  for (uint32_t g = xcd_wave_item(n_grp, nw); g < n_grp; g += nw) {
-    const uint32_t t0 = g * KEEP_GROUP, t1 = min(t0 + KEEP_GROUP, n_tl);
-    uint32_t mine = 0;
-    const uint32_t info = bid_info(fo, t0, t1, P->min_track_hits);
-    int32_t first[KEEP_GROUP];
-    first_rows(fo, t0, info, first);
+  const uint64_t below = (1ull << lane) - 1ull;
+  for (uint32_t i = xcd_wave_item(n_grp, nw); i < n_grp; i += nw) {
+    const uint32_t t0 = i * KEEP_GROUP, t1 = min(t0 + KEEP_GROUP, n_tl);
+    const BidGroup g = bid_group(fo, t0, t1, P->min_track_hits);
+    uint32_t n[KEEP_GROUP] = {};  // kept so far (uniform)
+    for (uint32_t e0 = lane; e0 - lane < g.tot; e0 += 64 * KEEP_CHUNKS) {
+      BidRow x[KEEP_CHUNKS];
 #pragma unroll
-    for (int kk = 0; kk < KEEP_GROUP; ++kk) {
-      const uint32_t t = t0 + kk;
-      if (t >= t1) continue;
-      uint32_t n = 0;
-      const uint32_t inf = (uint32_t)__builtin_amdgcn_readlane((int)info, kk);
-      if (inf) {
-        const uint32_t key = track_key((inf >> 8) & 255, t);
-        const int lo = (inf >> 16) & 255, hi = inf >> 24;
-        const int32_t* H = fo.hits + (size_t)t * NROW;
-        uint8_t* KR = fo.krow + (size_t)t * NROW;
-        for (int r0 = lo; r0 <= hi; r0 += 64) {
-          const int r = r0 + (int)lane;
-          bool kept = false;
-          if (r <= hi) {
-            const int32_t c = r0 == lo ? first[kk] : H[r];
-            kept = c >= 0 && (uint32_t)c < n_cl_cap && owner[c] == key;
-          }
-          const uint64_t m = __ballot(kept);
-          if (kept) KR[n + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint8_t)r;
-          n += (uint32_t)__popcll(m);
+      for (int m = 0; m < KEEP_CHUNKS; ++m) x[m] = bid_row(g, fo, t0, e0 + 64 * m, n_cl_cap);
+      uint32_t o[KEEP_CHUNKS];
+#pragma unroll
+      for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0u;  // no key is 0
+#pragma unroll
+      for (int m = 0; m < KEEP_CHUNKS; ++m) {
+        const bool kept = o[m] == track_key((x[m].info >> 8) & 255, t0 + x[m].k);
+        uint32_t at = 0;
+#pragma unroll
+        for (int k = 0; k < KEEP_GROUP; ++k) {
+          const uint64_t mask = __ballot(kept && x[m].k == (uint32_t)k);
+          if (x[m].k == (uint32_t)k) at = n[k] + (uint32_t)__popcll(mask & below);
+          n[k] += (uint32_t)__popcll(mask);
         }
-        if ((int)n < P->min_track_hits) n = 0;
+        if (kept) fo.krow[(size_t)(t0 + x[m].k) * NROW + at] = (uint8_t)x[m].r;
       }
-      if (lane == (uint32_t)kk) mine = n;
     }
+    uint32_t mine = 0;  // lane k: kept by the k-th
+#pragma unroll
+    for (int k = 0; k < KEEP_GROUP; ++k)
+      if (lane == (uint32_t)k && (int)n[k] >= P->min_track_hits) mine = n[k];
     if (t0 + lane < t1) {
       nkept[t0 + lane] = (uint16_t)mine;
       key[t0 + lane] = (uint8_t)mine;  // sort key of the refit (n <= NROW)

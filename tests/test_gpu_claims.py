@@ -1,0 +1,48 @@
+"""Conflict resolution on its own: from the exported hit tables, every cluster
+goes to the tracklet with most hits (the lower index on a tie) and a track keeps
+the hits it won, recomputed here and compared exactly.  Numbers of tracklets
+around the groups of four that a wave takes, up to a full collision."""
+import numpy as np
+import pytest
+
+import tpcsynth
+from paper_2208_07412_amd import tpc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("tracks,sectors", [(1, 1), (2, 1), (3, 1), (5, 1), (9, 1), (60, 1),
+                                            (400, 1), (3000, 36)])
+def test_claims_from_hit_tables(tracks, sectors):
+    cfg = tpcsynth.config_small(tracks) if sectors == 1 else tpcsynth.config_c2()
+    ev = tpcsynth.generate(cfg, 77)
+    mc, mt = ev.n_samples // 4 + 64, ev.n_samples // 16 + 64
+    reco = tpc.Reco(ev.n_units, ev.n_time_bins, mc, mt, max_samples=ev.n_samples)
+    try:
+        zs = tpc.to_device_zs(ev.pad, ev.time, ev.adc, ev.row_start, ev.n_units, ev.n_time_bins)
+        cl, links = reco.alloc_clusters(ev.n_units, ev.n_time_bins, mc), reco.alloc_links(mc)
+        tl, tr = reco.alloc_tracklets(mt), reco.alloc_tracks(mt, mc, mc, mt)
+        reco.process(zs, cl, links, tl, tr)
+        c = reco.sync()
+        out = tpc.tracks_to_host(tr, c["n_clusters"], c["n_tracklets"])
+        min_hits = reco.params.min_track_hits
+    finally:
+        reco.close()
+    H = out["follow_hits"].astype(np.int64)
+    nh = (H >= 0).sum(1)
+    bids = nh >= min_hits
+    key = (nh << 24) | (0xFFFFFF - np.arange(len(H)))
+    owner = np.zeros(c["n_clusters"], np.int64)
+    for t in np.nonzero(bids)[0]:
+        np.maximum.at(owner, H[t][H[t] >= 0], key[t])
+    won = (H >= 0) & bids[:, None] & (owner[np.maximum(H, 0)] == key[:, None])
+    n = won.sum(1)
+    hs, tlt = out["hit_start"].astype(np.int64), out["tracklet"]
+    assert np.array_equal(np.diff(hs), n[tlt]) and (n[tlt] >= min_hits).all()
+    for j, t in enumerate(tlt):
+        assert np.array_equal(out["hits"][hs[j]:hs[j + 1]], H[t][won[t]])
+    ct = np.full(c["n_clusters"], -1)
+    ct[out["hits"]] = np.repeat(np.arange(len(tlt)), np.diff(hs))
+    assert np.array_equal(out["cluster_track"], ct)
+    # what kept enough hits and is no track failed its refit
+    assert (n >= min_hits).sum() - len(tlt) <= c["n_refit_fail"] + c["n_fallback_fail"]
