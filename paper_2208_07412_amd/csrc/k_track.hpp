@@ -1190,15 +1190,18 @@ __device__ __forceinline__ BidRow bid_row(const BidGroup& g, const FollowOut& fo
 
 // Every followed tracklet with enough hits bids for its clusters: the owner
 // of a cluster is the largest key among its bidders.  Two launches instead of
-// one atomicMax per hit: FIX = false stores a bidder's key where the owner it
-// reads is smaller (of bidders that read at the same time one lands); FIX = true
-// reads the owner back and raises it with atomicMax only where the bidder's key
-// is larger.  Owners hold bidders' keys and only grow in the second launch, so
-// the largest bidder either reads its own key or raises the owner to it: the
-// result is the maximum.  Most clusters have one bidder and cost a load and a
-// plain store instead of a device-scope atomic, and most of the others have the
-// largest before the second launch (storing without the look: 668 us for claims
-// and keep on a 2 ms slice, with it 578).
+// one atomicMax per hit: FIX = false stores every bidder's key (one of them
+// lands); FIX = true reads the owner back and raises it with atomicMax only
+// where the bidder's key is larger.  Owners only grow in the second launch
+// and hold bidders' keys, so the largest bidder either reads its own key or
+// raises the owner to it: the result is the maximum.  Most clusters have one
+// bidder and cost a plain store and a load instead of a device-scope atomic.
+// (The first launch must not look at the owner before it stores, though that
+// saves most of the raises, 578 us for claims and keep on a 2 ms slice: two XCDs
+// that have read a line and then store to one word of it can be left with
+// different values, so that the second launch reads the larger on one of them
+// while the smaller is in memory; a cluster in ten million went to the wrong
+// tracklet, with several streams at work.)
 template <bool FIX>
 __global__ __launch_bounds__(256) void k_claim(FollowOut fo, const uint32_t* n_tl_dev,
                                                uint32_t tl_cap,
@@ -1224,15 +1227,16 @@ __global__ __launch_bounds__(256) void k_claim(FollowOut fo, const uint32_t* n_t
 #pragma unroll
       for (int m = 0; m < KEEP_CHUNKS; ++m) x[m] = bid_row(g, fo, t0, e0 + 64 * m, n_cl_cap);
       uint32_t o[KEEP_CHUNKS];
+      if (FIX) {
 #pragma unroll
-      for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0xFFFFFFFFu;
+        for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0xFFFFFFFFu;
+      }
 #pragma unroll
       for (int mm = 0; mm < KEEP_CHUNKS; ++mm) {
         const int m = FIX ? mm : KEEP_CHUNKS - 1 - mm;
         const uint32_t key = track_key((x[m].info >> 8) & 255, t0 + x[m].k);
-        if (o[m] >= key) continue;
-        if (FIX) atomicMax(&owner[x[m].c], key);
-        else owner[x[m].c] = key;
+        if (!FIX && x[m].c >= 0) owner[x[m].c] = key;
+        if (FIX && o[m] < key) atomicMax(&owner[x[m].c], key);
       }
     }
   }

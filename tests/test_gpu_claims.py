@@ -4,9 +4,12 @@ the hits it won, recomputed here and compared exactly.  Numbers of tracklets
 around the groups of four that a wave takes, up to a full collision."""
 import numpy as np
 import pytest
+import torch
 
 import tpcsynth
-from paper_2208_07412_amd import tpc
+from paper_2208_07412_amd import pipeline, tpc
+
+from _parity import run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +49,25 @@ def test_claims_from_hit_tables(tracks, sectors):
     assert np.array_equal(out["cluster_track"], ct)
     # what kept enough hits and is no track failed its refit
     assert (n >= min_hits).sum() - len(tlt) <= c["n_refit_fail"] + c["n_fallback_fail"]
+
+
+def test_claims_with_streams_at_work():
+    # four parts on streams of their own, again and again: every pass has the
+    # hits of one call over the whole frame
+    ev = tpcsynth.generate(tpcsynth.config_chunk(404, 3, n_coll=6), 4043)
+    full = run_gpu(ev, moments=False, follow=False)["tracks"]["hits"].astype(np.int64)
+    zs = tpc.to_device_zs(ev.pad, ev.time, ev.adc, ev.row_start, ev.n_units, ev.n_time_bins)
+    p = pipeline.Pipeline(zs, 4, stagger="none")
+    want = None
+    for i in range(200):
+        p.enqueue()
+        torch.cuda.synchronize()
+        got = [sl.tr["hits"][:int(sl.tr["n_hits"].item())].clone() for sl in p.slices]
+        if want is None:
+            off = np.cumsum([0] + [int(sl.cl["n_clusters"].item()) for sl in p.slices])
+            n = np.cumsum([0] + [len(g) for g in got])
+            assert n[-1] == len(full)
+            want = [torch.from_numpy((full[n[k]:n[k + 1]] - off[k]).astype(np.int32)).cuda()
+                    for k in range(4)]
+        assert all(torch.equal(g, w) for g, w in zip(got, want)), i
+    p.close()
