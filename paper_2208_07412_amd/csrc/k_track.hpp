@@ -329,6 +329,7 @@ struct FollowOut {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 // Raw buffer resource over a device array (uniform base, no range limit:
 // callers read inside the array; word 3 = 32-bit data format).
@@ -622,10 +623,34 @@ struct FollowLane {
   int32_t pre;    // candidate of the next row known before its helix step, or -1
   uint32_t ubase;
   int r, r1, L, nmiss, nh, hi, lo, rs;  // rs: row of sp
-  int pend_row;       // row whose hit-table entry is still to be stored, or -1
-  int32_t pend_hit;
+  i32x4 quad;   // hit-table entries of the four rows about row r
+  i32x4 lower;  // pass B: of the four rows below them
+  int pend;     // last row whose entry in quad is not stored yet, or -1
   uint32_t n_steps, n_cands, n_upds;      // work done (measurement)
 };
+
+// The hit table is read and written four rows at a time: a lane's tracklet has
+// lines of its own, and with an entry at a time the lines of all the lanes in
+// flight did not stay in the caches (the two passes of a 2 ms slice 1286 and 1142 us,
+// with four at a time 969 and 986).
+static_assert(NROW % 4 == 0, "whole quads");
+__device__ __forceinline__ int32_t quad_get(i32x4 v, int row) {
+  const int m = row & 3;
+  return m < 2 ? (m == 0 ? v.x : v.y) : (m == 2 ? v.z : v.w);
+}
+__device__ __forceinline__ void quad_set(i32x4& v, int row, int32_t hit) {
+  const int m = row & 3;
+  v.x = m == 0 ? hit : v.x;
+  v.y = m == 1 ? hit : v.y;
+  v.z = m == 2 ? hit : v.z;
+  v.w = m == 3 ? hit : v.w;
+}
+// The entries of the four rows below `row`'s four, if pass A wrote any of them.
+__device__ __forceinline__ i32x4 quad_lower(const FollowLane& f, const FollowOut& fo, int row) {
+  const int r0 = (row & ~3) - 4;
+  if (r0 + 3 < f.r1) return i32x4{-1, -1, -1, -1};
+  return *reinterpret_cast<const i32x4*>(fo.hits + (size_t)f.t * NROW + r0);
+}
 
 // Seed and first update of tracklet t; false if it cannot be followed.
 __device__ __forceinline__ bool follow_init(FollowLane& f, uint32_t t, const ClusterView& cl,
@@ -680,7 +705,8 @@ __device__ __forceinline__ bool follow_init(FollowLane& f, uint32_t t, const Clu
   c0_reset(k, pv, r1);
   f.n_upds += 1;
   if (!update(k, k.p[0], 0.0f, s_inverse(k, pv.vy(r1), pv.vz(r1)))) return false;
-  if (lead) fo.hits[(size_t)t * NROW + r1] = (int32_t)A;
+  f.quad = (int32_t)A;  // (entries of rows that no pass visits are not read)
+  f.pend = r1;
   f.nh = 1;
 #pragma unroll
   for (int i = 0; i < 5; ++i) f.sp[i] = k.p[i];
@@ -689,21 +715,23 @@ __device__ __forceinline__ bool follow_init(FollowLane& f, uint32_t t, const Clu
   f.hi = r1;
   f.pre = L > 1 ? upc[A] : -1;  // the next row is on the tracklet's own chain
   f.r = r1;
-  f.pend_row = -1;
   return true;
 }
 
-// The pending hit-table store of a tracklet.  A row's entry is stored while
-// the next row's helix step runs (or at the end of the pass): the waits on the
-// loads that follow a store also wait for the store to complete, and issued at
-// the end of its own step it would hold up the next one.
+// Stores the hit-table entries about row r (QUAD), or that of row r (in quad.x).
+template <bool QUAD>
 __device__ __forceinline__ void follow_flush(FollowLane& f, const FollowOut& fo, bool lead) {
-  if (f.pend_row >= 0 && lead) fo.hits[(size_t)f.t * NROW + f.pend_row] = f.pend_hit;
-  f.pend_row = -1;
+  int32_t* H = fo.hits + (size_t)f.t * NROW;
+  if (f.pend >= 0 && lead) {
+    if (QUAD) *reinterpret_cast<i32x4*>(H + (f.pend & ~3)) = f.quad;
+    else H[f.pend] = f.quad.x;
+  }
+  f.pend = -1;
 }
 
 // Pass B start: the outermost pass-A hit (row rs) with a reset covariance;
 // false if its update fails (the tracklet then ends with the pass-A state).
+template <bool QUAD>
 __device__ __forceinline__ bool follow_start_b(FollowLane& f, const ClusterView& cl,
                                                const FollowOut& fo, const PV<float>& pv) {
   Trk<float>& k = f.k;
@@ -711,7 +739,17 @@ __device__ __forceinline__ bool follow_start_b(FollowLane& f, const ClusterView&
   for (int i = 0; i < 5; ++i) k.p[i] = f.sp[i];
   c0_reset(k, pv, f.rs);
   f.lo = f.r1;
-  const int32_t co = fo.hits[(size_t)f.t * NROW + f.rs];
+  const int32_t* H = fo.hits + (size_t)f.t * NROW;
+  int32_t co;
+  if (QUAD) {
+    f.quad = *reinterpret_cast<const i32x4*>(H + (f.rs & ~3));
+    f.lower = quad_lower(f, fo, f.rs);
+    co = quad_get(f.quad, f.rs);
+  } else {
+    co = H[f.rs];
+    f.pre = f.rs - 1 >= f.r1 ? H[f.rs - 1] : -1;
+  }
+  f.pend = -1;
   const int2 q = cl.pos[co];
   const float my = (float)q.x * (float)FX_SCALE;
   const float mz = (float)(q.y - f.anchor) * (float)FX_SCALE;
@@ -721,8 +759,6 @@ __device__ __forceinline__ bool follow_start_b(FollowLane& f, const ClusterView&
   for (int i = 0; i < 5; ++i) f.sp[i] = k.p[i];
   f.nmiss = 0;
   f.r = f.rs;
-  f.pre = f.rs - 1 >= f.r1 ? fo.hits[(size_t)f.t * NROW + f.rs - 1] : -1;
-  f.pend_row = -1;
   return true;
 }
 
@@ -740,7 +776,7 @@ __device__ __forceinline__ void follow_finish(const FollowLane& f, FollowOut& fo
 // One row of pass A (outward, PA = 1) or pass B (inward, PA = 0).  Returns
 // true when the pass has ended.  With a group of G lanes per tracklet, lane
 // sub = 0 of the group writes.
-template <int PA>
+template <int PA, bool QUAD = true>
 __device__ __forceinline__ bool follow_step(FollowLane& f, const ClusterView& cl,
                                             const uint32_t* cblk, uint32_t nblk,
                                             const int32_t* upc, FollowOut& fo, const DevParams32* P,
@@ -750,20 +786,27 @@ __device__ __forceinline__ bool follow_step(FollowLane& f, const ClusterView& cl
   const bool lead = sub == 0;
   const int rn = f.r + (pa ? 1 : -1);
   if (rn >= NROW || rn < 0) return true;
-  int32_t* H = fo.hits + (size_t)f.t * NROW;
+  if (QUAD && (rn & 3) == (pa ? 0 : 3)) {  // into the next four rows
+    follow_flush<QUAD>(f, fo, lead);
+    if (!pa) {
+      f.quad = f.lower;
+      f.lower = quad_lower(f, fo, rn);
+    }
+  }
   // Rows whose candidate is known before the helix step: the tracklet's own
   // chain (pass A) and the rows pass A covered (pass B: its hit, or -1 for a
-  // row it missed, which is searched).  The candidate's position and the
-  // next row's known candidate are loaded before the step, so their latency
-  // overlaps its arithmetic.
+  // row it missed, which is searched).  The candidate's position and the chain's
+  // next candidate are loaded before the step, so their latency overlaps its
+  // arithmetic.
   const bool known = pa ? rn < f.r1 + f.L : rn >= f.r1;
-  int32_t cand = known ? f.pre : -1;
+  int32_t cand = !known ? -1 : pa || !QUAD ? f.pre : quad_get(f.quad, rn);
   int2 q = make_int2(0, 0);
   if (cand >= 0) q = cl.pos[cand];
   const int rn2 = rn + (pa ? 1 : -1);
   int32_t pre2 = -1;
-  if (pa ? (rn2 < f.r1 + f.L && cand >= 0) : (rn2 >= f.r1 && rn2 >= 0)) pre2 = pa ? upc[cand] : H[rn2];
-  follow_flush(f, fo, lead);
+  if (pa ? (rn2 < f.r1 + f.L && cand >= 0) : (!QUAD && rn2 >= f.r1))
+    pre2 = pa ? upc[cand] : fo.hits[(size_t)f.t * NROW + rn2];
+  if (!QUAD) follow_flush<QUAD>(f, fo, lead);
   Trk<float>& k = f.k;
   // the row's constants in one round of LDS reads, before the step
   const float dx = row_dx<float>(P, f.r, rn);
@@ -778,17 +821,19 @@ __device__ __forceinline__ bool follow_step(FollowLane& f, const ClusterView& cl
                       sub);
     fresh = true;
   }
-  f.pre = pre2;
+  if (pa || !QUAD) f.pre = pre2;
   f.r = rn;
+  auto entry = [&](int32_t hit) {
+    if (QUAD) quad_set(f.quad, rn, hit);
+    else f.quad.x = hit;
+    f.pend = rn;
+  };
   // a row this pass visits first gets exactly one store: its hit, or -1
   const bool first = pa || (fresh && rn < f.lo);
   if (pa) f.hi = rn;
   else if (first) f.lo = rn;
   if (cand < 0) {
-    if (first) {
-      f.pend_row = rn;
-      f.pend_hit = -1;
-    }
+    if (first) entry(-1);
     if ((pa || rn < f.r1) && ++f.nmiss >= P->max_miss) return true;
     return false;
   }
@@ -796,15 +841,11 @@ __device__ __forceinline__ bool follow_step(FollowLane& f, const ClusterView& cl
   const float mz = (float)(q.y - f.anchor) * (float)FX_SCALE;
   ++f.n_upds;
   if (!update(k, my, mz, si)) {
-    if (first) {
-      f.pend_row = rn;
-      f.pend_hit = -1;
-    }
+    if (first) entry(-1);
     return true;
   }
   if (pa || fresh) {
-    f.pend_row = rn;
-    f.pend_hit = cand;
+    entry(cand);
     ++f.nh;
   }
 #pragma unroll
@@ -888,16 +929,16 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
     if (PASS != FP_B) {
       while (!follow_step<1>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max)) {
       }
-      follow_flush(f, fo, true);
+      follow_flush<true>(f, fo, true);
     }
     if (PASS == FP_A) {
       f.lo = f.r1;
       follow_finish(f, fo);
       key[t] = (uint8_t)f.rs;
-    } else if (follow_start_b(f, cl, fo, pv)) {
+    } else if (follow_start_b<true>(f, cl, fo, pv)) {
       while (!follow_step<0>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max)) {
       }
-      follow_flush(f, fo, true);
+      follow_flush<true>(f, fo, true);
       follow_finish(f, fo);
     } else if (PASS == FP_AB) {
       follow_finish(f, fo);
@@ -1004,19 +1045,22 @@ __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* 
       if (PASS == FP_B) {
         if (fo.ok[t]) {
           follow_resume(f, t, cl, tl_start, tl_len, pts, fo);
-          busy = follow_start_b(f, cl, fo, pv);
+          busy = follow_start_b<false>(f, cl, fo, pv);
         }
       } else {
         busy = follow_init(f, t, cl, tl_start, tl_len, upc, pts, fo, P, pv, lead);
         if (!busy && lead) key[t] = 0;
       }
       if (busy) {
-        while (!follow_step<PASS == FP_A ? 1 : 0>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max, G,
+        // (few waves: the caches hold their lines, and an entry at a time takes
+        // fewer instructions of the one long chain)
+        constexpr bool quad = false;
+        while (!follow_step<PASS == FP_A ? 1 : 0, quad>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max, G,
                                                   sub)) {
           if (COUNT) ++w_iter;
         }
         if (COUNT) ++w_iter;
-        follow_flush(f, fo, lead);
+        follow_flush<quad>(f, fo, lead);
         if (PASS == FP_A) f.lo = f.r1;
         if (lead) {
           follow_finish(f, fo);
@@ -1052,7 +1096,7 @@ __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* 
           if (PASS == FP_B) {
             if (fo.ok[t]) {
               follow_resume(f, t, cl, tl_start, tl_len, pts, fo);
-              busy = follow_start_b(f, cl, fo, pv);
+              busy = follow_start_b<true>(f, cl, fo, pv);
             }
           } else {
             busy = follow_init(f, t, cl, tl_start, tl_len, upc, pts, fo, P, pv);
@@ -1065,7 +1109,7 @@ __global__ __launch_bounds__(B) void k_follow_q(ClusterView cl, const uint32_t* 
     if (COUNT) ++w_iter;
     if (busy && follow_step<PASS == FP_A ? 1 : 0>(f, cl, cblk, nblk, upc, fo, P, pv, chi2max)) {
       busy = false;
-      follow_flush(f, fo, true);
+      follow_flush<true>(f, fo, true);
       if (PASS == FP_A) {
         f.lo = f.r1;
         follow_finish(f, fo);
