@@ -78,12 +78,6 @@ __device__ __forceinline__ void latch_capacity(DevStatus* st, int kind, uint32_t
 // at the start of every workgroup).
 __device__ __forceinline__ bool failed(const DevStatus* st) { return st->status != 0; }
 
-__device__ __forceinline__ int64_t floor_div64(int64_t a, int64_t b) {  // b > 0
-  int64_t q = a / b;
-  if ((a % b != 0) && (a < 0)) --q;
-  return q;
-}
-
 // Bijective remap of a 1-D grid so that consecutive logical blocks land on
 // the same XCD (blocks are dispatched round-robin over 8 XCDs), which keeps
 // neighbouring tiles in one L2.
@@ -162,15 +156,27 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
   return v;
 }
 
+// Over the 64 lanes of a wave, all of them active: within rows of 16, then
+// across the rows (lanes that a move does not reach keep their own value).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t dpp_or_own(int32_t v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, ROWS, 0xF, false);
+}
+template <class F>
+__device__ __forceinline__ int32_t wave_reduce_i32(int32_t v, F f) {
+  v = f(v, dpp_or_own<0x111, 0xF>(v));
+  v = f(v, dpp_or_own<0x112, 0xF>(v));
+  v = f(v, dpp_or_own<0x114, 0xF>(v));
+  v = f(v, dpp_or_own<0x118, 0xF>(v));
+  v = f(v, dpp_or_own<0x142, 0xA>(v));
+  v = f(v, dpp_or_own<0x143, 0xC>(v));
+  return __builtin_amdgcn_readlane(v, 63);
+}
 __device__ __forceinline__ int32_t wave_min_i32(int32_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v = min(v, __shfl_xor(v, d, 64));
-  return v;
+  return wave_reduce_i32(v, [](int32_t a, int32_t b) { return min(a, b); });
 }
 __device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v = max(v, __shfl_xor(v, d, 64));
-  return v;
+  return wave_reduce_i32(v, [](int32_t a, int32_t b) { return max(a, b); });
 }
 __device__ __forceinline__ unsigned long long wave_sum_u64(uint32_t v) {
   unsigned long long x = v;

@@ -61,8 +61,8 @@ __global__ __launch_bounds__(256) void k_hit_grid(ClusterView cl, const uint16_t
 __device__ __forceinline__ void nb_candidates(const ClusterView& cl, const uint32_t* cblk,
                                               uint32_t nblk, uint32_t ur, int64_t z, int64_t wz,
                                               uint32_t& a, uint32_t& b) {
-  const int64_t lo = floor_div64(z - wz, 32768) - 3;
-  const int64_t hi = floor_div64(z + wz, 32768) + 3;
+  const int64_t lo = ((z - wz) >> 15) - 3;  // (the shift rounds down)
+  const int64_t hi = ((z + wz) >> 15) + 3;
   int32_t blo = lo < 0 ? 0 : (int32_t)(lo >> CG_BSHIFT);
   int32_t bhi = hi < 0 ? -1 : (int32_t)(hi >> CG_BSHIFT);
   if (blo > (int32_t)nblk - 1) blo = nblk - 1;
@@ -72,40 +72,44 @@ __device__ __forceinline__ void nb_candidates(const ClusterView& cl, const uint3
 }
 
 // Best (j, k) pair for cluster i among the candidates [ja, jb) in row r-1
-// and [ka, kb) in row r+1 (positions pos[]).  The k candidates inside the
-// window are marked once in a 64-bit mask when the range has at most 64
-// (most of a time window's candidates lie outside the y window), else listed
-// in registers (up to NB_KLIST; beyond that the whole range is scanned per
-// j).  Positions are below 2^30 in magnitude and
-// windows are capped at 2^30 (far beyond any row), so every difference fits
-// 32 bits and a score (sum of two squares) fits 64 bits unsigned; the
-// decision is the exact integer one.
+// and [ka, kb) in row r+1 (positions pos[]).  The candidates inside the window
+// are marked once in masks of 32 bits when neither range has more (most of a time
+// window's candidates lie outside the y window; masks of 64 bits for the few
+// longer ranges were slower than the lists, 426 against 388 us); else the k
+// candidates are listed in registers (up to NB_KLIST; beyond that the whole range
+// is scanned per j).  Positions are below 2^30 in magnitude and windows are capped at 2^30
+// (far beyond any row), so every difference fits 32 bits and a score (sum of two
+// squares) fits 64 bits unsigned; the decision is the exact integer one.  The
+// kernel is bound by these instructions: with a 64-bit mask of the k candidates,
+// two comparisons per coordinate and reductions through LDS permutations the
+// kernel took 620 us on a 2 ms slice, 388 with the masks of both rows, one
+// unsigned comparison and lane moves.
 #define NB_KLIST 8
-__device__ __forceinline__ bool nb_in(int32_t a, int32_t b, int32_t w) {
-  const int32_t d = a - b;
-  return d <= w && d >= -w;
-}
 template <class PJ, class PK>
 __device__ __forceinline__ void nb_best(PJ J, PK K, int32_t yi, int32_t zi, int32_t wy,
                                         int32_t wz, uint64_t smax, uint32_t ja, uint32_t jb,
                                         uint32_t ka, uint32_t kb, int32_t& bd, int32_t& bu) {
-  if (kb - ka <= 64) {
-    // the in-window k candidates as a bit mask, walked in ascending order
-    uint64_t km = 0;
-    for (uint32_t k = ka; k < kb; ++k) {
-      const int2 pk = K(k);
-      if (nb_in(pk.x, yi, wy) && nb_in(pk.y, zi, wz)) km |= 1ull << (k - ka);
-    }
+  // |p - (y, z)| <= (w, w) as one unsigned comparison per coordinate (positions
+  // below 2^30 and windows up to 2^30: no difference wraps into the window)
+  const uint32_t y0 = (uint32_t)yi - (uint32_t)wy, y2 = 2u * (uint32_t)wy;
+  const uint32_t z0 = (uint32_t)zi - (uint32_t)wz, z2 = 2u * (uint32_t)wz;
+  auto in = [&](int2 p) { return (uint32_t)p.x - y0 <= y2 && (uint32_t)p.y - z0 <= z2; };
+  if (kb - ka <= 32 && jb - ja <= 32) {
+    // the in-window candidates of both rows as bit masks, walked in ascending
+    // order
+    uint32_t km = 0, jm = 0;
+    for (uint32_t k = ka, bit = 1; k < kb; ++k, bit += bit) km |= in(K(k)) ? bit : 0u;
     if (km == 0) return;
+    for (uint32_t j = ja, bit = 1; j < jb; ++j, bit += bit) jm |= in(J(j)) ? bit : 0u;
     uint64_t best = ~0ull;
-    for (uint32_t j = ja; j < jb; ++j) {
+    for (; jm != 0; jm &= jm - 1) {
+      const uint32_t j = ja + (uint32_t)__builtin_ctz(jm);
       const int2 pj = J(j);
-      if (!nb_in(pj.x, yi, wy) || !nb_in(pj.y, zi, wz)) continue;
-      const int32_t ay = yi - pj.x, az = zi - pj.y;
-      for (uint64_t m = km; m != 0; m &= m - 1) {
-        const uint32_t k = ka + (uint32_t)__builtin_ctzll(m);
+      const uint32_t ay = 2u * (uint32_t)yi - (uint32_t)pj.x, az = 2u * (uint32_t)zi - (uint32_t)pj.y;
+      for (uint32_t m = km; m != 0; m &= m - 1) {
+        const uint32_t k = ka + (uint32_t)__builtin_ctz(m);
         const int2 pk = K(k);
-        const int32_t dy = ay + (yi - pk.x), dz = az + (zi - pk.y);
+        const int32_t dy = (int32_t)(ay - (uint32_t)pk.x), dz = (int32_t)(az - (uint32_t)pk.y);
         const uint64_t sc = (uint64_t)((int64_t)dy * dy) + (uint64_t)((int64_t)dz * dz);
         // j and k ascend, so a strict "<" keeps the smallest (j, k) on ties
         if (sc <= smax && sc < best) {
@@ -122,7 +126,7 @@ __device__ __forceinline__ void nb_best(PJ J, PK K, int32_t yi, int32_t zi, int3
   bool over = false;
   for (uint32_t k = ka; k < kb; ++k) {
     const int2 pk = K(k);
-    if (!nb_in(pk.x, yi, wy) || !nb_in(pk.y, zi, wz)) continue;
+    if (!in(pk)) continue;
     if (nk < NB_KLIST) {
 #pragma unroll
       for (int m = 0; m < NB_KLIST; ++m)
@@ -136,7 +140,7 @@ __device__ __forceinline__ void nb_best(PJ J, PK K, int32_t yi, int32_t zi, int3
   uint64_t best = ~0ull;
   for (uint32_t j = ja; j < jb; ++j) {
     const int2 pj = J(j);
-    if (!nb_in(pj.x, yi, wy) || !nb_in(pj.y, zi, wz)) continue;
+    if (!in(pj)) continue;
     // 2 y_i - y_j - y_k = (y_i - y_j) + (y_i - y_k), each term inside its window
     const int32_t ay = yi - pj.x, az = zi - pj.y;
     auto consider = [&](uint32_t k, int2 pk) {
@@ -158,7 +162,7 @@ __device__ __forceinline__ void nb_best(PJ J, PK K, int32_t yi, int32_t zi, int3
     } else {
       for (uint32_t k = ka; k < kb; ++k) {
         const int2 pk = K(k);
-        if (!nb_in(pk.x, yi, wy) || !nb_in(pk.y, zi, wz)) continue;
+        if (!in(pk)) continue;
         consider(k, pk);
       }
     }
