@@ -293,25 +293,30 @@ struct EmitStart {
   }
 };
 
-// Length of the chain of every listed start (0 below min_tracklet).  Chains
-// cross one row per link, so a walk longer than 152 means corrupt links and
-// is cut.
+// Length of the chain of every listed start (0 below min_tracklet), with its
+// middle and end clusters for the following (one walk for both: a second one
+// over the tracklets took 18 us of a sector and 89 of a 2 ms slice).  Chains cross
+// one row per link, so a walk longer than 152 means corrupt links and is cut.
 __global__ void k_chain_len(const uint32_t* __restrict__ cand, const uint32_t* n_cand_dev,
                             uint32_t cand_cap, const int32_t* __restrict__ upc,
                             const uint32_t* n_cl_dev, uint32_t n_cl_cap,
-                            uint16_t* __restrict__ len, const DevParams* __restrict__ P,
+                            uint16_t* __restrict__ len, uint2* __restrict__ mid_end,
+                            const DevParams* __restrict__ P,
                             const DevStatus* st) {
   if (failed(st)) return;
   const uint32_t n = scan_count(n_cand_dev, cand_cap);
   const uint32_t n_cl = scan_count(n_cl_dev, n_cl_cap);
   uint32_t dp;
   for (uint32_t p = xcd_thread_item(n, dp); p < n; p += dp) {
-    uint32_t L = 1;
-    int32_t c = upc[cand[p]];
+    uint32_t L = 1, m = cand[p], e = m;
+    int32_t c = upc[m];
     while (c >= 0 && (uint32_t)c < n_cl && L < NROW) {
       ++L;
+      e = (uint32_t)c;
       c = upc[c];
+      if (L & 1) m = (uint32_t)upc[m];  // element (L + 1) / 2 - 1 of the chain
     }
+    mid_end[p] = make_uint2(m, e);
     if ((int)L < P->min_tracklet) L = 0;
     len[p] = (uint16_t)L;
   }
@@ -325,13 +330,18 @@ struct GetKeepLen {
 struct EmitTracklet {
   const uint32_t* cand;
   const uint16_t* len;
+  const uint2* mid_end;
   uint32_t* start;
   uint16_t* out_len;
+  uint32_t* pts;
   uint32_t capacity;
   __device__ void operator()(uint32_t p, uint32_t pos, uint32_t v) const {
     if (v && pos < capacity) {
       start[pos] = cand[p];
       out_len[pos] = len[p];
+      const uint2 me = mid_end[p];
+      pts[(size_t)pos * 3 + 0] = me.x;
+      pts[(size_t)pos * 3 + 1] = me.y;
     }
   }
 };

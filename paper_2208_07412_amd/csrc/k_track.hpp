@@ -435,7 +435,8 @@ __device__ __forceinline__ int32_t search_row(const ClusterView& cl, const uint3
   return best;
 }
 
-// Per tracklet (a walk of its cleaned up-links): its middle and end clusters
+// Per tracklet (by a walk of its cleaned up-links, unless the walk for the chain
+// lengths has left them in pts): its middle and end clusters
 // (0xFFFFFFFF for a tracklet that cannot be followed: broken chain or rows
 // beyond the last), its start unit-row, and the sort key of the outward
 // following pass: the rows above its start row (the most rows that pass can
@@ -447,7 +448,7 @@ __global__ __launch_bounds__(256) void k_tracklet_points(ClusterView cl, uint32_
                                                          const uint32_t* n_tl_dev, uint32_t tl_cap,
                                                          uint32_t* __restrict__ pts,
                                                          uint8_t* __restrict__ key,
-                                                         uint32_t* __restrict__ qnext,
+                                                         uint32_t* __restrict__ qnext, int walked,
                                                          DevStatus* st) {
   // the counters of the fit stage and the queue counters of its following
   if (blockIdx.x == 0 && threadIdx.x < 2 * XCD_GROUPS) {
@@ -470,7 +471,11 @@ __global__ __launch_bounds__(256) void k_tracklet_points(ClusterView cl, uint32_
         const int im = (L + 1) / 2 - 1;
         uint32_t c = A, m = A;
         bool bad = false;
-        for (int i = 1; i < L; ++i) {
+        if (walked) {  // pts holds them, from the chains' lengths
+          m = pts[(size_t)t * 3 + 0];
+          c = pts[(size_t)t * 3 + 1];
+        }
+        for (int i = walked ? L : 1; i < L; ++i) {
           const int32_t nx = upc[c];
           if (nx < 0 || (uint32_t)nx >= n_cl) {
             bad = true;

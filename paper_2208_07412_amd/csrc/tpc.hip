@@ -67,6 +67,7 @@ struct tpc_ctx {
   void* bsum = nullptr;       // scan block sums (u64)
   uint32_t* tot32 = nullptr;
   uint16_t* chain_len = nullptr;  // per listed chain start
+  uint2* chain_me = nullptr;  // middle and end cluster per chain start
   uint32_t* cand = nullptr;       // chain starts, ascending
   uint8_t* start_flag = nullptr;  // 1 where a chain starts (per cluster)
   int32_t* f_hits = nullptr;
@@ -129,7 +130,7 @@ struct Layout {
 };
 
 struct Plan {
-  size_t zblk, cblk, win, cl_list, crec, bsum, tot32, chain_len, cand, start_flag, f_hits, f_state, f_nhits, f_range, f_ok, f_pts, f_key, f_perm, f_bins, f_krow, f_work, f_qnext, pos,
+  size_t zblk, cblk, win, cl_list, crec, bsum, tot32, chain_len, chain_me, cand, start_flag, f_hits, f_state, f_nhits, f_range, f_ok, f_pts, f_key, f_perm, f_bins, f_krow, f_work, f_qnext, pos,
       owner, nkept, r_par, r_cov, r_chi2, r_row, r_flags, trk_index, qc_part, zp_off, cm_a, cm_b, cm_res, cm_tot, cm_info, mg_fs,
       mg_cell, mg_cnt, mg_off, mg_cur, mg_parent, mg_key, mg_idx, mg_skey, mg_sidx,
       mg_sector, mg_C, mg_tgl, mg_e, mg_cs18, mg_pos, mg_dir, mg_hxy, hit_off, par, st, total;
@@ -180,6 +181,7 @@ Plan plan_for(const tpc_sizes& m) {
   p.bsum = L.add<unsigned long long>(p.bsum_cap);
   p.tot32 = L.add<uint32_t>(1);
   p.chain_len = L.add<uint16_t>(mc / 2 + 1);
+  p.chain_me = L.add<uint2>(mc / 2 + 1);
   p.cand = L.add<uint32_t>(mc / 2 + 1);
   p.start_flag = L.add<uint8_t>(mc);
   p.f_hits = L.add<int32_t>(mt * NROW);
@@ -568,15 +570,18 @@ int stage_tracklets(tpc_ctx* c, const tpc_clusters* cl, tpc_links* l, tpc_trackl
   run_scan<uint32_t>(c, GetStart{c->start_flag}, EmitStart{c->cand, capc},
                      StoreFin<uint32_t>{c->tot32}, cl->n_clusters, cap);
   k_chain_len<<<grid_for(capc, 256, kCapStream), 256, 0, s>>>(c->cand, c->tot32, capc, l->upc, cl->n_clusters,
-                                                  cap, c->chain_len, c->d_par, c->d_st);
+                                                  cap, c->chain_len, c->chain_me, c->d_par, c->d_st);
   run_scan<uint32_t>(c, GetKeepLen{c->chain_len},
-                     EmitTracklet{c->cand, c->chain_len, t->start, t->len, t->capacity},
+                     EmitTracklet{c->cand, c->chain_len, c->chain_me, t->start, t->len, c->f_pts,
+                                  t->capacity},
                      FinTracklets{t->capacity, t->n_tracklets, c->d_st}, c->tot32, capc);
   return launch_ok();
 }
 
+// walked: stage_tracklets has just left the tracklets' points in f_pts (a caller's
+// tracklets are walked here).
 int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_tracklets* t,
-              tpc_tracks* tr) {
+              tpc_tracks* tr, bool walked) {
   hipStream_t s = c->stream;
   const uint32_t n_ur = cl->n_units * NROW;
   const uint32_t nblk = ceil_div(cl->n_time_bins, 1u << CG_BSHIFT);
@@ -611,7 +616,7 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
     StageTimer tm(c, 6);  // the tracklets' seed points belong to tracklet building
     k_tracklet_points<<<grid_for(tcap, 256, kCapStream), 256, 0, s>>>(cv, n_ur, l->upc, t->start, t->len,
                                                            t->n_tracklets, tcap, c->f_pts,
-                                                           c->f_key, c->f_qnext, c->d_st);
+                                                           c->f_key, c->f_qnext, walked, c->d_st);
   }
   {
     StageTimer tm(c, 7);
@@ -840,6 +845,7 @@ int tpc_create(tpc_ctx** out, const tpc_params* p, const tpc_sizes* max, void* h
   c->bsum = base + pl.bsum;
   c->tot32 = (uint32_t*)(base + pl.tot32);
   c->chain_len = (uint16_t*)(base + pl.chain_len);
+  c->chain_me = (uint2*)(base + pl.chain_me);
   c->cand = (uint32_t*)(base + pl.cand);
   c->start_flag = (uint8_t*)(base + pl.start_flag);
   c->f_hits = (int32_t*)(base + pl.f_hits);
@@ -1143,7 +1149,7 @@ int tpc_fit_tracks(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const
     return TPC_ERR_ARG;
   int rc = stage_grid(c, cl);
   if (rc) return rc;
-  return stage_fit(c, cl, l, t, tr);
+  return stage_fit(c, cl, l, t, tr, false);
 }
 
 static_assert(QC_BINS == TPC_QC_BINS && QC_QTOT == TPC_QC_QTOT && QC_QMAX == TPC_QC_QMAX &&
@@ -1236,7 +1242,7 @@ int tpc_process_timeframe(tpc_ctx* c, const tpc_zs_input* in, tpc_clusters* cl, 
   if (!rc) rc = stage_grid(c, cl);
   if (!rc) rc = stage_neighbours(c, cl, l);
   if (!rc) rc = stage_tracklets(c, cl, l, t);
-  if (!rc) rc = stage_fit(c, cl, l, t, tr);
+  if (!rc) rc = stage_fit(c, cl, l, t, tr, true);
   return rc;
 }
 

@@ -47,3 +47,25 @@ def test_same_results(event, mc, mt):
     for a, b in zip(got[1:], ref[1:]):
         for k in b:
             assert np.array_equal(a[k], b[k]), k
+
+
+def test_stages_equal_the_whole(event):
+    # called stage by stage the fit walks the tracklets itself
+    ev, ref = event
+    mc, mt = 15000, 4000
+    reco = tpc.Reco(ev.n_units, ev.n_time_bins, mc, mt, max_samples=ev.n_samples)
+    try:
+        zs = tpc.to_device_zs(ev.pad, ev.time, ev.adc, ev.row_start, ev.n_units, ev.n_time_bins)
+        cl, links = reco.alloc_clusters(ev.n_units, ev.n_time_bins, mc), reco.alloc_links(mc)
+        tl, tr = reco.alloc_tracklets(mt), reco.alloc_tracks(mt, mc, mc)
+        reco.cluster(zs, cl)
+        reco.find_neighbours(cl, links)
+        reco.build_tracklets(cl, links, tl)
+        reco.fit_tracks(cl, links, tl, tr)
+        c = reco.sync()
+        got = tpc.tracklets_to_host(tl), tpc.tracks_to_host(tr, c["n_clusters"])
+    finally:
+        reco.close()
+    for a, b in zip(got, ref[3:5]):
+        for k in b:
+            assert np.array_equal(a[k], b[k]), k
