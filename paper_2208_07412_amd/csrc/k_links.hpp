@@ -105,7 +105,8 @@ __device__ __forceinline__ void nb_best(PJ J, PK K, int32_t yi, int32_t zi, int3
     for (; jm != 0; jm &= jm - 1) {
       const uint32_t j = ja + (uint32_t)__builtin_ctz(jm);
       const int2 pj = J(j);
-      const uint32_t ay = 2u * (uint32_t)yi - (uint32_t)pj.x, az = 2u * (uint32_t)zi - (uint32_t)pj.y;
+      const uint32_t ay = 2u * (uint32_t)yi - (uint32_t)pj.x;
+      const uint32_t az = 2u * (uint32_t)zi - (uint32_t)pj.y;
       for (uint32_t m = km; m != 0; m &= m - 1) {
         const uint32_t k = ka + (uint32_t)__builtin_ctz(m);
         const int2 pk = K(k);

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256, 4) void k_mg_pairs(
     if (!last && t < total) {
       me = pos[t];
       const uint32_t cell = cell_of_end[me.id];
-      const uint32_t zb = cell % nzb, ix = (cell / nzb) % MG_NXY, iy = (cell / nzb / MG_NXY) % MG_NXY;
+      const uint32_t zb = cell % nzb, xy = cell / nzb, ix = xy % MG_NXY, iy = xy / MG_NXY % MG_NXY;
       const uint32_t up = zb + 1 < nzb ? 1 : 0, dn = zb > 0 ? 1 : 0;
       if (run == 0) {
         k0 = t + 1;
@@ -434,10 +434,12 @@ __global__ __launch_bounds__(256, 4) void k_mg_pairs(
   if (lane < rn) mg_pair_check(S, ra[w][lane], rb[w][lane], parent, near_tie);
 }
 
-// Global position and drift of every hit of every track (the fit reads the position three times):
-// one thread per hit, its cluster's (unit,row) found by a binary search of the
-// row starts (one lane per track walking its hits took 0.68 ms on a 2 ms
-// Pb-Pb slice, the longest tracks setting the pace; per hit: 0.21 ms).
+// Global position and drift of every hit of every track (the fit reads the
+// positions three times): one thread per hit, its cluster's (unit,row) found by a
+// binary search of the row starts (one lane per track walking its hits took 0.68
+// ms on a 2 ms Pb-Pb slice, the longest tracks setting the pace; per hit: 0.28 ms,
+// bound by the gathers of the clusters: the search's first steps in LDS took no
+// more than 6% off).
 __global__ void k_mg_hits(const uint32_t* __restrict__ crow, uint32_t n_ur,
                           const int32_t* __restrict__ y_fx, const int32_t* __restrict__ z_fx,
                           const uint32_t* n_cl_dev, uint32_t cl_cap,

@@ -1576,7 +1576,7 @@ __device__ int refit_seed(uint32_t t, const ClusterView& cl, int32_t anchor, con
 // with their rounding errors.  A low-pT track (|q/pT| >= lowpt_qpt at the
 // seed) whose FP32 covariance loses positive definiteness is refit again in
 // FP64 from its seed by the same lane (TF_TO_FP64 marks it; the mark is
-// internal and counted by a reduction); force_fallback sends every track
+// internal, the count an atomic per wave); force_fallback sends every track
 // there (a test hook).
 __global__ __launch_bounds__(64) void k_refit(ClusterView cl, const uint32_t* __restrict__ tl_start,
                                               FollowOut fo, const uint32_t* n_tl_dev,
