@@ -83,3 +83,11 @@ def test_shared_windows(name, w, k):
                 tuning=dict(cl_window=w, cl_chunk=k, cl_mode=2))
     o = run_oracle(ev, labels=True)
     compare_clusters(g["clusters"], o["clusters"], labels=True)
+
+
+@pytest.mark.parametrize("bins", [53 * 512, 53 * 512 + 1])
+def test_windows_per_workgroup_by_frame_size(bins):
+    # 8056 and 8208 workgroups of 16 windows: 8 windows each below the line, 16 above
+    ev = event(noise(bins, 0.002, (0, 75, 151), 3), bins)
+    g, o = run_gpu(ev, labels=True, max_tracklets=4096), run_oracle(ev, labels=True)
+    compare_clusters(g["clusters"], o["clusters"], labels=True)
