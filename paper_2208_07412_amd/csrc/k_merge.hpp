@@ -3,8 +3,8 @@
 //
 // A segment's two ends (innermost and outermost hit) carry their global
 // position, drift z and the tangent of the segment's outward fit there.  Ends
-// are binned by (frame, side, 30.5 cm squares of the bending plane, 36 cm of
-// drift); one lane per end finds the ends close to it in the 3 x 3 x 3 cells
+// are binned by (frame, side, 30.5 cm squares of the bending plane, 12 cm of
+// drift); one lane per end finds the ends close to it in the 3 x 3 x 7 cells
 // around it (every joinable pair has ends within 35 cm in drift and 30 cm in the
 // bending plane, so the cells hold all candidates); the pairs go through the
 // joining rule, and join segments by a lock-free union-find that always hangs the larger root under
@@ -29,7 +29,11 @@
 #define MG_DC_ABS 1e-3
 #define MG_C_LINE 1e-4
 #define MG_TIE 1e-9
-#define MG_ZBIN 36.0  // drift cell (cm), above MG_DZMAX
+// drift cells (cm), MG_ZR of which are above MG_DZMAX (fewer candidates outside the
+// gate in finer ones: 37 collisions merged in 808, 792, 772 and 779 us with MG_ZR
+// 1, 2, 3 and 4)
+#define MG_ZR 3
+#define MG_ZBIN (36.0 / MG_ZR)
 #define MG_XYBIN 30.5  // bending-plane cell (cm), above MG_GAP with its tie band
 #define MG_XY0 260.0   // the cells cover [-MG_XY0, MG_XY0) in x and y (outer radius ~247 cm)
 #define MG_NXY 18      // cells per axis: ceil(2 MG_XY0 / MG_XYBIN)
@@ -311,16 +315,16 @@ __device__ __forceinline__ void mg_pair_check(const MgSegs& S, uint32_t e, uint3
 
 // One lane per end, ends taken in cell order (the lanes of a wave mostly
 // share their cells and so scan the same neighbour cells in step).  Of the
-// 3 x 3 x 3 cells around an end half are scanned, so that a pair is met once:
-// the rest of its own cell and the cell above in drift, and four neighbouring
-// columns of three drift cells, each a run of consecutive ends.  A wave takes
+// 3 x 3 x 7 cells around an end half are scanned, so that a pair is met once:
+// the rest of its own cell and the MG_ZR cells above in drift, and four neighbouring
+// columns of 2 MG_ZR + 1 drift cells, each a run of consecutive ends.  A wave takes
 // 64 ends and one of the five runs at a time (a grid of a few waves per SIMD
 // strides over these), four candidates loaded together and the next four on
 // their way.  Pairs that pass the gates on drift z and distance go to a queue of
 // the wave in LDS, and every 64 of them are tested in FP32 by the 64 lanes
 // together; the few that FP32 cannot rule out go to a second queue for the FP64
 // test (two helix extrapolations with an arc tangent each), 64 at a time again.
-// On a chunk of 37 collisions (139,000 segments) 342 us; 1364 with one wave per 64
+// On a chunk of 37 collisions (139,000 segments) 316 us; 1364 with one wave per 64
 // ends for all 27 cells, every gated pair tested in FP64, a candidate at a time.
 #define MG_SCAN 4
 #define MG_RUNS 5
@@ -354,7 +358,7 @@ __global__ __launch_bounds__(256, 4) void k_mg_pairs(
       me = pos[t];
       const uint32_t cell = cell_of_end[me.id];
       const uint32_t zb = cell % nzb, xy = cell / nzb, ix = xy % MG_NXY, iy = xy / MG_NXY % MG_NXY;
-      const uint32_t up = zb + 1 < nzb ? 1 : 0, dn = zb > 0 ? 1 : 0;
+      const uint32_t up = min((uint32_t)MG_ZR, nzb - 1 - zb), dn = min((uint32_t)MG_ZR, zb);
       if (run == 0) {
         k0 = t + 1;
         len = cell_off[cell + up + 1] - k0;
@@ -708,7 +712,7 @@ __device__ __forceinline__ void mg_fit_rows(const uint32_t* __restrict__ skey,
 // Bound by the FP64 instructions and the LDS traffic on large frames, where 8
 // lanes per component waste fewer of both (half of 16 have no sum to add up),
 // and on small ones by the longest component, whose hits are one chain that 16
-// lanes shorten: on 139,000 segments 240 us with 8 lanes, 305 with 16 and 566
+// lanes shorten: on 139,000 segments 219 us with 8 lanes, 305 with 16 and 566
 // with one; the whole call on one small collision 128, 111 and 350 us.  Four waves
 // per SIMD, so the arrays are read eight values at a time: with both widths in the
 // kernel the compiler's own choice of 172 registers took 299 us on the large one.
