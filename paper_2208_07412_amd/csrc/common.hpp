@@ -75,8 +75,19 @@ __device__ __forceinline__ void latch_capacity(DevStatus* st, int kind, uint32_t
 
 // An error latched by an earlier launch (a plain load: what this launch
 // latches itself need not be seen, and an atomic load would go past the caches
-// at the start of every workgroup).
+// at the start of every workgroup).  Where a launch latches errors itself, its
+// waves may see them or not, each on its own: failed_wg is for those whose waves
+// share LDS.
 __device__ __forceinline__ bool failed(const DevStatus* st) { return st->status != 0; }
+
+// failed() as one thread sees it, for the whole workgroup (all threads call it):
+// no wave leaves while another goes on to LDS that both were to fill.
+__device__ __forceinline__ bool failed_wg(const DevStatus* st) {
+  __shared__ int32_t status;
+  if (threadIdx.x == 0) status = st->status;
+  __syncthreads();
+  return status != 0;
+}
 
 // Bijective remap of a 1-D grid so that consecutive logical blocks land on
 // the same XCD (blocks are dispatched round-robin over 8 XCDs), which keeps

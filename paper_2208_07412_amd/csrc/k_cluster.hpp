@@ -1091,7 +1091,7 @@ __global__ __launch_bounds__(64 * NW) void k_cluster_peaks_mw(ZsArgs in,
                                                              const DevParams* __restrict__ P,
                                                              DevStatus* st) {
   __shared__ PeaksLdsMw<W, NW> L;
-  if (failed(st)) return;
+  if (failed_wg(st)) return;
   peaks_chunk_mw<W, K, NW, PRE>(in, zblk, nblk, nwin, nchunk, n_ur, win_cnt, rec, sample_label, P,
                                 st, xcd_remap(blockIdx.x, gridDim.x), L);
 }

@@ -596,7 +596,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   __shared__ uint32_t h[256];
   __shared__ int32_t xs[NROW];
   __shared__ CmTrackLds lds[4];
-  if (failed(st)) return;
+  if (failed_wg(st)) return;
   for (uint32_t i = threadIdx.x; i < 256; i += blockDim.x) h[i] = 0;
   for (uint32_t i = threadIdx.x; i < NROW; i += blockDim.x) xs[i] = P->xfx[i];
   __syncthreads();
@@ -1425,7 +1425,7 @@ __global__ __launch_bounds__(256) void k_cm_dec_tracks(const uint32_t* __restric
                                                        CmDecOut o, DevStatus* st) {
   __shared__ uint32_t stage[4][CM_STAGE_WORDS];
   __shared__ int32_t xs[NROW];  // row radii: the helix steps read them per lane
-  if (failed(st) || !info[6]) return;
+  if (failed_wg(st) || !info[6]) return;
   for (uint32_t i = threadIdx.x; i < NROW; i += blockDim.x) xs[i] = P->xfx[i];
   __syncthreads();
   const uint32_t nu = info[0], nt = info[1], nc = info[2];

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void k_hit_grid(ClusterView cl, const uint16_t
                                                   int2* __restrict__ pos,
                                                   uint32_t* __restrict__ owner,
                                                   const DevParams* __restrict__ P, DevStatus* st) {
-  if (failed(st)) return;
+  if (failed_wg(st)) return;
   if (blockIdx.x < n_ur) {
     block_index<true>(cl.ptime, ppad, nullptr, cl.crow, n_ur, nblk, CG_BSHIFT, T, cl.capacity, blk,
                       P, st, 0, n_ur);

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(ZSP_BLOCK) void k_zs_decode(const uint32_t* __restr
   __shared__ uint16_t run_of[ZSP_MAX_SAMPLES];
   __shared__ uint32_t lds_scan[ZSP_BLOCK / 64 + 1];
   __shared__ int bad;
-  if (failed(st)) return;
+  if (failed_wg(st)) return;
   const bool validate = P->validate != 0;
   const uint4* src = reinterpret_cast<const uint4*>(pages);
   uint32_t p = blockIdx.x;
