@@ -1319,10 +1319,11 @@ __global__ __launch_bounds__(256) void k_keep(FollowOut fo, const uint32_t* n_tl
       for (int m = 0; m < KEEP_CHUNKS; ++m) x[m] = bid_row(g, fo, t0, e0 + 64 * m, n_cl_cap);
       uint32_t o[KEEP_CHUNKS];
 #pragma unroll
-      for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0u;  // no key is 0
+      for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0u;
 #pragma unroll
       for (int m = 0; m < KEEP_CHUNKS; ++m) {
-        const bool kept = o[m] == track_key((x[m].info >> 8) & 255, t0 + x[m].k);
+        // (not by the owner alone: the key of tracklet 2^24 - 1 is 0 if it does not bid)
+        const bool kept = x[m].c >= 0 && o[m] == track_key((x[m].info >> 8) & 255, t0 + x[m].k);
         uint32_t at = 0;
 #pragma unroll
         for (int k = 0; k < KEEP_GROUP; ++k) {
