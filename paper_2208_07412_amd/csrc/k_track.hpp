@@ -1179,36 +1179,52 @@ __device__ __forceinline__ uint32_t track_key(uint32_t nh, uint32_t t) {
   return (nh << 24) | (0xFFFFFFu - t);
 }
 
-// Conflict resolution runs one wave per tracklet: the lanes take the rows
-// of the tracklet's hit table (contiguous), so every table read is coalesced.
-// The tracklet index is made wave-uniform so its scalars load once.
-
-// A wave takes KEEP_GROUP consecutive tracklets and the rows of their hit
-// tables one after the other, 64 to a chunk, KEEP_CHUNKS chunks at a time: their
-// hits are loaded together, then the hits' owners.  Bound by the gathers of
-// owners, a line each (on a 2 ms slice the three kernels took 745 us with a
-// tracklet at a time, 64 rows to a load, 668 this way; 741 with 8 tracklets; a
-// tracklet per lane, 64 of them over one row after the other, was slower, 880: the
-// lanes' hits share few lines, and more claims were stored twice).
+// Conflict resolution: a wave takes KEEP_GROUP consecutive tracklets and the rows
+// of their hit tables one after the other, 64 to a chunk, KEEP_CHUNKS chunks at a
+// time: their hits are loaded together, then the hits' owners.  Bound by the
+// gathers of owners, a line each (on a 2 ms slice the kernels, with every claim
+// stored and then looked at, took 745 us with a tracklet at a time, 64 rows to a
+// load, 668 this way; 741 with 8 tracklets; a tracklet per lane, 64 of them over one
+// row after the other, was slower, 880: the lanes' hits share few lines).
 #define KEEP_GROUP 4
 #define KEEP_CHUNKS 4
+// The rows of a tracklet that a kernel takes: all from its first to its last, those
+// of its chain, or the rest.
+enum { ROWS_ALL = 0, ROWS_CHAIN = 1, ROWS_REST = 2 };
 struct BidGroup {
   uint32_t info;  // lane k: 1 | hit count << 8 | row range << 16 of tracklet t0 + k if it
                   // bids (followed, at least min_track_hits hits), else 0
+  uint32_t rows;  // lane k: its first row | rows before the gap << 8 | rows of the gap << 16
   uint32_t pre;   // lane k: rows of the tracklets before it
   uint32_t tot;   // rows of the group
   uint32_t end[KEEP_GROUP];  // rows up to and with the k-th (uniform)
 };
-__device__ __forceinline__ BidGroup bid_group(const FollowOut& fo, uint32_t t0, uint32_t t1,
+// (pts and tl_len: the tracklets' start unit-rows and chain lengths, not read for
+// ROWS_ALL)
+template <int ROWS>
+__device__ __forceinline__ BidGroup bid_group(const FollowOut& fo, const uint32_t* pts,
+                                              const uint16_t* tl_len, uint32_t t0, uint32_t t1,
                                               int min_hits) {
   BidGroup g;
   const uint32_t t = t0 + (threadIdx.x & 63);
   g.info = 0;
+  g.rows = 0;
+  uint32_t len = 0;
   if (t < t1 && fo.ok[t]) {
     const uint32_t nh = fo.nhits[t];
-    if ((int)nh >= min_hits) g.info = 1u | (nh << 8) | ((uint32_t)fo.range[t] << 16);
+    if ((int)nh >= min_hits) {
+      g.info = 1u | (nh << 8) | ((uint32_t)fo.range[t] << 16);
+      const uint32_t lo = (g.info >> 16) & 255, hi = g.info >> 24;
+      g.rows = lo | 255u << 8;
+      len = hi - lo + 1;
+      if (ROWS != ROWS_ALL) {
+        const uint32_t r1 = pts[(size_t)t * 3 + 2] % NROW;  // lo <= r1 <= hi
+        const uint32_t n = min((uint32_t)tl_len[t], hi + 1 - r1);
+        g.rows = ROWS == ROWS_CHAIN ? r1 | 255u << 8 : lo | (r1 - lo) << 8 | n << 16;
+        len = ROWS == ROWS_CHAIN ? n : len - n;
+      }
+    }
   }
-  const uint32_t len = g.info ? (g.info >> 24) - ((g.info >> 16) & 255) + 1 : 0u;
   const uint32_t end = wave_incl_scan(len);
   g.pre = end - len;
 #pragma unroll
@@ -1224,6 +1240,7 @@ struct BidRow {
   uint32_t k, info;
   int32_t r, c;
 };
+template <int ROWS>
 __device__ __forceinline__ BidRow bid_row(const BidGroup& g, const FollowOut& fo, uint32_t t0,
                                           uint32_t e, uint32_t n_cl_cap) {
   BidRow x;
@@ -1231,29 +1248,37 @@ __device__ __forceinline__ BidRow bid_row(const BidGroup& g, const FollowOut& fo
 #pragma unroll
   for (int k = 0; k + 1 < KEEP_GROUP; ++k) x.k += e >= g.end[k];
   x.info = (uint32_t)__shfl((int)g.info, (int)x.k);
-  x.r = (int32_t)(((x.info >> 16) & 255) + e - (uint32_t)__shfl((int)g.pre, (int)x.k));
+  const uint32_t rows = (uint32_t)__shfl((int)g.rows, (int)x.k);
+  const uint32_t i = e - (uint32_t)__shfl((int)g.pre, (int)x.k);
+  x.r = (int32_t)((rows & 255) + i);
+  if (ROWS == ROWS_REST && i >= ((rows >> 8) & 255)) x.r += (int32_t)(rows >> 16);
   x.c = e < g.tot ? fo.hits[(size_t)(t0 + x.k) * NROW + x.r] : -1;
   if ((uint32_t)x.c >= n_cl_cap) x.c = -1;
   return x;
 }
 
-// Every followed tracklet with enough hits bids for its clusters: the owner
-// of a cluster is the largest key among its bidders.  Two launches instead of
-// one atomicMax per hit: FIX = false stores every bidder's key (one of them
-// lands); FIX = true reads the owner back and raises it with atomicMax only
-// where the bidder's key is larger.  Owners only grow in the second launch
-// and hold bidders' keys, so the largest bidder either reads its own key or
-// raises the owner to it: the result is the maximum.  Most clusters have one
-// bidder and cost a plain store and a load instead of a device-scope atomic.
-// (The first launch must not look at the owner before it stores, though that
-// saves most of the raises, 578 us for claims and keep on a 2 ms slice: two XCDs
-// that have read a line and then store to one word of it can be left with
-// different values, so that the second launch reads the larger on one of them
-// while the smaller is in memory; a cluster in ten million went to the wrong
-// tracklet, with several streams at work.)
-template <bool FIX>
-__global__ __launch_bounds__(256) void k_claim(FollowOut fo, const uint32_t* n_tl_dev,
-                                               uint32_t tl_cap,
+// Every followed tracklet with enough hits bids for its clusters: the owner of a
+// cluster is the largest key among its bidders.  The owners start at 0, below
+// every key.
+// The tracklets of stage_tracklets take two launches: ROWS_CHAIN stores the key of
+// each at the clusters of its own chain; ROWS_REST looks at the owners of its other
+// clusters and raises them by atomicMax where its key is larger.  A cluster lies in
+// one chain at most (a cleaned link is its two clusters' choice of each other, so no
+// cluster is the upper end of two, and a chain starts at a cluster that is the upper
+// end of none): the first launch writes no word twice, and the second one reads and
+// writes by atomics of the device's scope, so that the result is the maximum
+// whichever workgroups run on whichever XCD.
+// A caller's tracklets may overlap: ROWS_ALL, one atomicMax per hit, in one launch.
+// Whole calls, with every key stored and then looked at by plain loads (which
+// leaves open what a load finds where two XCDs have stored to one word), with the
+// chains' keys stored, and with ROWS_ALL: 2 ms slice 6030, 6090 and 6439 us; 20
+// stressed collisions 2472, 2509 and 2499; one central collision 1128, 1127 and
+// 1128; fit of ten collisions 1078, 1086 and 1088.  With every key stored by
+// device-scope atomics and looked at: 6334, 2558, 1136 and 1117.
+template <int ROWS>
+__global__ __launch_bounds__(256) void k_claim(FollowOut fo, const uint32_t* __restrict__ pts,
+                                               const uint16_t* __restrict__ tl_len,
+                                               const uint32_t* n_tl_dev, uint32_t tl_cap,
                                                uint32_t* __restrict__ owner,
                                                uint32_t n_cl_cap, const DevParams* __restrict__ P,
                                                const DevStatus* st) {
@@ -1263,29 +1288,25 @@ __global__ __launch_bounds__(256) void k_claim(FollowOut fo, const uint32_t* n_t
   const uint32_t n_grp = (n_tl + KEEP_GROUP - 1) / KEEP_GROUP;
   uint32_t nw;
   for (uint32_t i = xcd_wave_item(n_grp, nw); i < n_grp; i += nw) {
-    // the stores go in descending tracklet order, so that of two bidders with
-    // equal hit counts the one that wins (the lower index) tends to store
-    // last (a store order sorted by key wins more clusters at once but loses
-    // the locality of neighbouring tracklets and costs more than it saves)
-    const uint32_t t0 = (FIX ? i : n_grp - 1 - i) * KEEP_GROUP, t1 = min(t0 + KEEP_GROUP, n_tl);
-    const BidGroup g = bid_group(fo, t0, t1, P->min_track_hits);
-    const uint32_t nb = (g.tot + 64 * KEEP_CHUNKS - 1) / (64 * KEEP_CHUNKS);
-    for (uint32_t j = 0; j < nb; ++j) {
-      const uint32_t e0 = (FIX ? j : nb - 1 - j) * 64 * KEEP_CHUNKS + lane;
+    const uint32_t t0 = i * KEEP_GROUP, t1 = min(t0 + KEEP_GROUP, n_tl);
+    const BidGroup g = bid_group<ROWS>(fo, pts, tl_len, t0, t1, P->min_track_hits);
+    for (uint32_t e0 = lane; e0 - lane < g.tot; e0 += 64 * KEEP_CHUNKS) {
       BidRow x[KEEP_CHUNKS];
 #pragma unroll
-      for (int m = 0; m < KEEP_CHUNKS; ++m) x[m] = bid_row(g, fo, t0, e0 + 64 * m, n_cl_cap);
+      for (int m = 0; m < KEEP_CHUNKS; ++m) x[m] = bid_row<ROWS>(g, fo, t0, e0 + 64 * m, n_cl_cap);
       uint32_t o[KEEP_CHUNKS];
-      if (FIX) {
 #pragma unroll
-        for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0xFFFFFFFFu;
+      for (int m = 0; m < KEEP_CHUNKS; ++m) {
+        o[m] = x[m].c >= 0 ? 0u : 0xFFFFFFFFu;  // (nothing to claim)
+        if (ROWS == ROWS_REST && x[m].c >= 0)
+          o[m] = __hip_atomic_load(&owner[x[m].c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
 #pragma unroll
-      for (int mm = 0; mm < KEEP_CHUNKS; ++mm) {
-        const int m = FIX ? mm : KEEP_CHUNKS - 1 - mm;
+      for (int m = 0; m < KEEP_CHUNKS; ++m) {
         const uint32_t key = track_key((x[m].info >> 8) & 255, t0 + x[m].k);
-        if (!FIX && x[m].c >= 0) owner[x[m].c] = key;
-        if (FIX && o[m] < key) atomicMax(&owner[x[m].c], key);
+        if (o[m] >= key) continue;
+        if (ROWS == ROWS_CHAIN) owner[x[m].c] = key;
+        else atomicMax(&owner[x[m].c], key);
       }
     }
   }
@@ -1311,12 +1332,13 @@ __global__ __launch_bounds__(256) void k_keep(FollowOut fo, const uint32_t* n_tl
   const uint64_t below = (1ull << lane) - 1ull;
   for (uint32_t i = xcd_wave_item(n_grp, nw); i < n_grp; i += nw) {
     const uint32_t t0 = i * KEEP_GROUP, t1 = min(t0 + KEEP_GROUP, n_tl);
-    const BidGroup g = bid_group(fo, t0, t1, P->min_track_hits);
+    const BidGroup g = bid_group<ROWS_ALL>(fo, nullptr, nullptr, t0, t1, P->min_track_hits);
     uint32_t n[KEEP_GROUP] = {};  // kept so far (uniform)
     for (uint32_t e0 = lane; e0 - lane < g.tot; e0 += 64 * KEEP_CHUNKS) {
       BidRow x[KEEP_CHUNKS];
 #pragma unroll
-      for (int m = 0; m < KEEP_CHUNKS; ++m) x[m] = bid_row(g, fo, t0, e0 + 64 * m, n_cl_cap);
+      for (int m = 0; m < KEEP_CHUNKS; ++m)
+        x[m] = bid_row<ROWS_ALL>(g, fo, t0, e0 + 64 * m, n_cl_cap);
       uint32_t o[KEEP_CHUNKS];
 #pragma unroll
       for (int m = 0; m < KEEP_CHUNKS; ++m) o[m] = x[m].c >= 0 ? owner[x[m].c] : 0u;

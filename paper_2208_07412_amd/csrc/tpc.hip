@@ -720,9 +720,18 @@ int stage_fit(tpc_ctx* c, const tpc_clusters* cl, const tpc_links* l, const tpc_
   }
   {
     StageTimer tm(c, 8);
-    // one wave per tracklet, about 8 tracklets per wave
-    k_claim<false><<<gw, 256, 0, s>>>(fo, t->n_tracklets, tcap, c->owner, ccap, c->d_par, c->d_st);
-    k_claim<true><<<gw, 256, 0, s>>>(fo, t->n_tracklets, tcap, c->owner, ccap, c->d_par, c->d_st);
+    // a wave per KEEP_GROUP tracklets, about two groups per wave; chains of this
+    // library's own tracklets share no cluster, a caller's may
+    auto claim = [&](auto rows) {
+      k_claim<decltype(rows)::value><<<gw, 256, 0, s>>>(fo, c->f_pts, t->len, t->n_tracklets, tcap,
+                                                        c->owner, ccap, c->d_par, c->d_st);
+    };
+    if (walked) {
+      claim(std::integral_constant<int, ROWS_CHAIN>{});
+      claim(std::integral_constant<int, ROWS_REST>{});
+    } else {
+      claim(std::integral_constant<int, ROWS_ALL>{});
+    }
     k_keep<<<gw, 256, 0, s>>>(fo, t->n_tracklets, tcap, c->owner, ccap, c->nkept, c->f_key,
                               c->d_par, c->d_st);
   }
