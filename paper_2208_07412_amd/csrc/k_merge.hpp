@@ -227,8 +227,12 @@ __global__ void k_mg_fill_cells(const uint32_t* __restrict__ cell_of_end, const 
 }
 
 // A cut in FP32: clearly missed, or within a part in a thousand (a NaN counts
-// as within).  The FP32 errors stay below a third of that: positions are good to
-// 8e-6 cm, so distances off a circle to 1e-4 cm where the cut's margin is 5e-4.
+// as within).  The FP32 errors stay below a third of that: coordinates are good to
+// 8e-6 cm and steps to d = 2.3e-5, so distances off a circle to 1e-4 cm where the
+// cut's margin is 5e-4.  At a distance q |r| from the centre the arc is good to d / q
+// and the tangent's turn to d |C| / q: pairs near a centre go on to the FP64 test, and
+// with |C| + |tan lambda| / 8 < q the errors of the drift are below 2.5e-4 (the
+// margin is 1e-3) and those of the sine below 3e-5 (1e-4).
 __device__ __forceinline__ void mg_cut32(float v, float cut, bool& missed, bool& close) {
   missed |= v > cut * 1.001f;
   close |= !(v < cut * 0.999f || v > cut * 1.001f);
@@ -258,8 +262,9 @@ __device__ __forceinline__ void mg_follows32(const MgDir& a, const MgDir& b, flo
   k = k * t + 0.999999225f;
   const float arc = 2.0f * p * iqc * k, len = fabsf(arc);
   // either form, towards the centre or around the circle, beyond the error bounds
-  close |= fabsf(aC - (float)MG_C_LINE) < 1e-8f || !(c1 > 0.1f) || !(aC < 1.0f) ||
-           !(fabsf(a.tgl) < 8.0f);
+  // (one comparison for both limits; a NaN in either is close)
+  close |= fabsf(aC - (float)MG_C_LINE) < 1e-8f || !(c1 > 0.1f) ||
+           !(aC + 0.125f * fabsf(a.tgl) < fminf(q, 1.0f));
   mg_cut32(perp, (float)MG_PERP, missed, close);
   mg_cut32(len, (float)MG_GAP, missed, close);
   mg_cut32(fabsf(dz - a.tgl * arc), (float)MG_DZ + (float)MG_DZ_ARC * len, missed, close);
