@@ -107,7 +107,6 @@ struct tpc_ctx {
   double* mg_hxy = nullptr;  // hit positions
   size_t bsum_cap = 0;
   tpc_tuning tune;
-  bool tuned = false;  // the launch shapes were set by the caller
   // stage timing (measurement only)
   static constexpr int kProfCap = 64;
   bool prof_on = false;
@@ -514,17 +513,13 @@ int stage_cluster(tpc_ctx* c, const tpc_zs_input* in, tpc_clusters* out) {
                 out->qtot, out->qmax, out->ppad, out->ptime, out->flags, out->sp, out->st,
                 out->spp, out->stt, out->nsamp, out->sample_label};
   const ZsArgs za = zs_args(in);
-  // Unless the caller chose: 16 windows per workgroup where that leaves at least
-  // kLongChunks workgroups (32 per CU, four rounds of the resident ones), since the
-  // set-up of a chunk then weighs more than the workgroups lost.  Peak pass with 8 and
-  // 16 windows: 2 ms slice (115,000 workgroups of 16) 1583 and 1517 us, 5 stressed
-  // collisions (10,944) 1825 and 1746, one collision (5,472) 70 and 73, one sector
-  // (152) 23 and 29.
-  constexpr uint64_t kLongChunks = 8192;
-  const int w = c->tune.cl_window;
-  int k = c->tune.cl_chunk;
-  if (!c->tuned && (uint64_t)ceil_div(ceil_div(in->n_time_bins, (uint32_t)w), 16u) * n_ur >= kLongChunks)
-    k = 16;
+  // (16 windows per workgroup instead of the default 8 follow no rule by size: the
+  // peak pass of 36 sectors took 90 us with 8 and 124 with 16 at 700 time bins, 296
+  // and 319 at 2,000, 452 and 429 at 3,000, 549 and 616 at 3,800, 1101 and 1028 at
+  // 7,000, 1442 and 1574 at 9,900, 1546 and 1496 at 10,500, 2341 and 2486 at 16,000,
+  // 3009 and 2919 at 20,500, and no better with the windows split evenly: what a
+  // frame gains is the caller's to measure)
+  const int w = c->tune.cl_window, k = c->tune.cl_chunk;
   auto run = [&](auto W, auto K) {
     launch_cluster<decltype(W)::value, decltype(K)::value>(c, za, nblk_s, n_ur, co, out->n_clusters,
                                                            out->capacity, out->crow_start);
@@ -1370,7 +1365,6 @@ int tpc_set_tuning(tpc_ctx* c, const tpc_tuning* t) {
       t->refit_waves != 8)
     return TPC_ERR_ARG;
   c->tune = *t;
-  c->tuned = true;
   return TPC_OK;
 }
 
