@@ -68,7 +68,8 @@ typedef struct {
   int32_t min_tracklet;   /* minimum tracklet length (5) */
   int32_t max_miss;       /* consecutive empty rows that stop following (6) */
   int32_t min_track_hits; /* minimum hits of a kept track (15) */
-  int64_t win_y, win_z;   /* neighbour search windows, 2^-16 cm (2.5 cm) */
+  int64_t win_y, win_z;   /* neighbour search windows, 2^-16 cm (2.5 cm); more than
+                             2^30 (164 m) counts as 2^30 */
   int64_t s_max;          /* neighbour score cut (2^32 = 0.5 cm midpoint) */
   double chi2_max;        /* hit acceptance in following (16) */
   double snp_max;         /* |sin phi| that stops propagation (0.95) */
@@ -500,8 +501,8 @@ void* tpc_stream(tpc_ctx* ctx);
  * (peak finding and moments, one pass over the samples), 2 cluster scan,
  * 3 cluster output, 4 cluster grid, 5 neighbours, 6 tracklets (and their
  * seed points, timed inside the fit call), 7 following (sorts and passes),
- * 8 resolution, 9 refit (FP32, FP64 redo of failing low-pT tracks), 10 count of the FP64
- * redos, 11 track output, 12 raw ZS page decoding (tpc_decode_zs_pages),
+ * 8 resolution, 9 refit (FP32, FP64 redo of failing low-pT tracks, and the count of the
+ * redos), 10 nothing (once the count of the FP64 redos), 11 track output, 12 raw ZS page decoding (tpc_decode_zs_pages),
  * 13 compression (tpc_compress), 14 decompression (tpc_decompress), 15 merging
  * and the T0 fit (tpc_merge_tracks). */
 #define TPC_PROF_STAGES 16

@@ -385,20 +385,6 @@ __device__ __forceinline__ int up_code_of(const uint16_t* tile, int c, int qmin,
   return code | ((code == 5 && a >= qmin) ? 16 : 0);
 }
 
-// The peak test alone: the sample's key beats its 8 neighbours (earlier
-// neighbours may tie on ADC, later ones may not) and its ADC reaches qmin.
-__device__ __forceinline__ bool is_peak(const uint16_t* tile, int c, int qmin) {
-  const Row3 u = row3(tile, c - CL_TP), m = row3(tile, c), d = row3(tile, c + CL_TP);
-  const int a = m.m;
-  const int e = max(max(u.l, u.m), max(u.r, m.l));
-  const int l = max(max(m.r, d.l), max(d.m, d.r));
-  return a >= qmin && e <= a && l < a;
-}
-
-__device__ __forceinline__ uint32_t lanes_below() {
-  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-}
-
 template <int ROWS>
 __device__ __forceinline__ void clear_tile(uint16_t* tile) {
   constexpr int TILE = ROWS * CL_TP;
@@ -695,11 +681,6 @@ __device__ __forceinline__ int mw_offset(int code) {
   return (r - 1) * CL_TP + (code - 5 * r - 1);
 }
 
-// One array: moment sums | tile | the idle lanes' cell (column 2 of the row
-// behind) | peak lists and counts.  The sums and the lists are also the guards
-// that codes of the outermost rows and of the idle cell read (a row and two
-// cells on each side; nothing uses what comes of them).  11,488 bytes at W = 32:
-// a fourteenth workgroup per compute unit fits.
 // One array: moment sums | tile | the idle lanes' cell (column 2 of the row
 // behind) | peak lists and counts.  The sums and the lists are also the guards
 // that codes of the outermost rows and of the idle cell read (a row and two

@@ -77,8 +77,9 @@ __device__ __forceinline__ void nb_candidates(const ClusterView& cl, const uint3
 // window's candidates lie outside the y window; masks of 64 bits for the few
 // longer ranges were slower than the lists, 426 against 388 us); else the k
 // candidates are listed in registers (up to NB_KLIST; beyond that the whole range
-// is scanned per j).  Positions are below 2^30 in magnitude and windows are capped at 2^30
-// (far beyond any row), so every difference fits 32 bits and a score (sum of two
+// is scanned per j).  Differences of positions are below 2^31 in magnitude (drift
+// positions run up to 65,000 bins of 2^15) and windows are capped at 2^30, so a
+// difference inside them fits 32 bits, as does the sum of two, and a score (sum of two
 // squares) fits 64 bits unsigned; the decision is the exact integer one.  The
 // kernel is bound by these instructions: with a 64-bit mask of the k candidates,
 // two comparisons per coordinate and reductions through LDS permutations the
@@ -89,8 +90,9 @@ template <class PJ, class PK>
 __device__ __forceinline__ void nb_best(PJ J, PK K, int32_t yi, int32_t zi, int32_t wy,
                                         int32_t wz, uint64_t smax, uint32_t ja, uint32_t jb,
                                         uint32_t ka, uint32_t kb, int32_t& bd, int32_t& bu) {
-  // |p - (y, z)| <= (w, w) as one unsigned comparison per coordinate (positions
-  // below 2^30 and windows up to 2^30: no difference wraps into the window)
+  // |p - (y, z)| <= (w, w) as one unsigned comparison per coordinate: a difference d
+  // below 2^31 in magnitude and a window w up to 2^30 leave d + w above 2 w, modulo
+  // 2^32, wherever d is outside [-w, w]
   const uint32_t y0 = (uint32_t)yi - (uint32_t)wy, y2 = 2u * (uint32_t)wy;
   const uint32_t z0 = (uint32_t)zi - (uint32_t)wz, z2 = 2u * (uint32_t)wz;
   auto in = [&](int2 p) { return (uint32_t)p.x - y0 <= y2 && (uint32_t)p.y - z0 <= z2; };

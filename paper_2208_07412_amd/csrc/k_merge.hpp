@@ -40,8 +40,6 @@
 #define MG_FIT 12     // doubles per merged-track fit record
 
 struct MgSegs {  // per segment (track), device SoA
-  uint32_t* fs;  // frame * 2 + side, 0xFFFFFFFF = no hits
-  uint8_t* sector;
   double *C, *tgl;
   double* e;     // [n * 10]: per end X, Y, z, tx, ty
 };
@@ -102,15 +100,12 @@ __global__ void k_mg_segments(const uint32_t* __restrict__ crow, uint32_t n_ur,
       ok = c0 < n_cl && c1 < n_cl;
     }
     if (!ok) {
-      S.fs[j] = 0xFFFFFFFFu;
       cell_of_end[2 * j] = cell_of_end[2 * j + 1] = 0xFFFFFFFFu;
       continue;
     }
     const uint32_t ur0 = mg_ur_of(crow, n_ur, c0), ur1 = mg_ur_of(crow, n_ur, c1);
     const uint32_t unit = ur0 / NROW, sector = unit % 36;
     const uint32_t fs = (unit / 36) * 2 + sector / 18;
-    S.fs[j] = fs;
-    S.sector[j] = (uint8_t)sector;
     const double C = -bz_b * (double)par[(size_t)j * 5 + 4];
     S.C[j] = C;
     S.tgl[j] = (double)par[(size_t)j * 5 + 3];

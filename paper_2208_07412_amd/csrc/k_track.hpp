@@ -978,8 +978,9 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
 #define FOLLOW_REFILL 32
 // Waves of the lane-refill grid per compute unit.  Each lane gathers lines of
 // its own (hit grid, positions, hit table) that the L2 holds only while few
-// lanes compete for it: on a 2 ms Pb-Pb slice the two passes took 3.02, 2.53,
-// 2.41, 2.53 and 2.63 ms with 8, 12, 16, 20 and 24 waves per compute unit.
+// lanes compete for it: on a 2 ms Pb-Pb slice the following stage took 2.76, 2.14,
+// 1.92, 1.93 and 1.94 ms with 8, 12, 16, 20 and 24 waves per compute unit (and 1.97,
+// 1.91, 1.92, 1.93 and 2.01 ms with refills of 16, 24, 32, 40 and 48 lanes).
 #define FOLLOW_Q_WAVES_PER_CU 16
 // Few tracklets: a sort group that fills at most the lanes of
 // FOLLOW_SPREAD_WAVES waves (the resident grid of one group) has its tracklets
@@ -989,13 +990,15 @@ __global__ __launch_bounds__(B) void k_follow(ClusterView cl, const uint32_t* __
 // there the pass lasts as long as the instructions of the longest tracklet plus
 // what the wave's other lanes add (other branches, more candidates per search):
 // fewer tracklets per wave cost less per step, and idle SIMDs take the rest.
-// Following stage (both passes, sorts included), before -> after: 250 tracklets
-// 717 -> 512 us, 20,000 896 -> 597, 66,000 1071 -> 680, 178,000 1204 -> 1012.
-// Groups of 1 and 2 lanes at 20,000: 711 and 611 us (wider groups
-// have to agree through LDS and gained nothing); 128 and 256 waves per group at
-// 66,000: 1055 and 993 us, 512: 681.  Above 64 per wave (262,144 tracklets in
-// all) lanes are refilled from the queue instead: a 2 ms slice's 730,000 take
-// 2.37 ms there, and spreading them over more waves evicts lines (above).
+// Following stage (both passes, sorts included) from the queue and spread: 250
+// tracklets 725 and 486 us, 5,457 732 and 576, 20,000 863 and 602, 67,000 953 and
+// 669, 103,000 998 and 698, 141,000 1083 and 920, 179,000 1194 and 984, 240,000 1257
+// and 1148.  Groups of at most 1, 2 and 4 lanes at 5,457: 549, 559 and 576 us, at
+// 20,000: 648, 608 and 602, at 67,000: 739, 664 and 669 (wider groups have to agree
+// through LDS and gained nothing); 128, 256 and 512 waves per group at 67,000: 944,
+// 790 and 669 us.  Above 64 per wave (262,144 tracklets in all) lanes are refilled
+// from the queue instead: a 2 ms slice's 730,000 take 1.92 ms there, and spreading
+// them over more waves evicts lines (above).
 #define FOLLOW_SPREAD_WAVES 512
 #define FOLLOW_SPREAD_SLOTS 64
 #define FOLLOW_SPREAD_G 4

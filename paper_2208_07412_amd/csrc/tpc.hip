@@ -97,15 +97,13 @@ struct tpc_ctx {
   unsigned long long* cm_tot = nullptr;       // compression: bit totals
   uint32_t* cm_info = nullptr;                // compression: sizes of the stream
   // merging: per-segment ends, cells, union-find, member sort
-  uint32_t *mg_fs = nullptr, *mg_cell = nullptr, *mg_cnt = nullptr, *mg_off = nullptr,
+  uint32_t *mg_cell = nullptr, *mg_cnt = nullptr, *mg_off = nullptr,
            *mg_cur = nullptr, *mg_parent = nullptr, *mg_key = nullptr,
            *mg_idx = nullptr, *mg_skey = nullptr, *mg_sidx = nullptr;
-  uint8_t* mg_sector = nullptr;
   double *mg_C = nullptr, *mg_tgl = nullptr, *mg_e = nullptr, *mg_cs18 = nullptr;
   MgPos* mg_pos = nullptr;   // ends in cell order
   MgDir* mg_dir = nullptr;
   double* mg_hxy = nullptr;  // hit positions
-  size_t bsum_cap = 0;
   tpc_tuning tune;
   // stage timing (measurement only)
   static constexpr int kProfCap = 64;
@@ -131,10 +129,9 @@ struct Layout {
 
 struct Plan {
   size_t zblk, cblk, win, cl_list, crec, bsum, tot32, chain_len, chain_me, cand, start_flag, f_hits, f_state, f_nhits, f_range, f_ok, f_pts, f_key, f_perm, f_bins, f_krow, f_work, f_qnext, pos,
-      owner, nkept, r_par, r_cov, r_chi2, r_row, r_flags, trk_index, qc_part, zp_off, cm_a, cm_b, cm_res, cm_tot, cm_info, mg_fs,
+      owner, nkept, r_par, r_cov, r_chi2, r_row, r_flags, trk_index, qc_part, zp_off, cm_a, cm_b, cm_res, cm_tot, cm_info,
       mg_cell, mg_cnt, mg_off, mg_cur, mg_parent, mg_key, mg_idx, mg_skey, mg_sidx,
-      mg_sector, mg_C, mg_tgl, mg_e, mg_cs18, mg_pos, mg_dir, mg_hxy, hit_off, par, st, total;
-  size_t bsum_cap;
+      mg_C, mg_tgl, mg_e, mg_cs18, mg_pos, mg_dir, mg_hxy, hit_off, par, st, total;
   uint32_t nblk, nblk_s, nwin;
 };
 
@@ -170,7 +167,6 @@ Plan plan_for(const tpc_sizes& m) {
   if (mg_cells(m) > nscan) nscan = mg_cells(m);
   if (256ull * (ceil_div(m.max_tracklets, SORT_BLOCK) + XCD_GROUPS - 1) > nscan)
     nscan = 256ull * (ceil_div(m.max_tracklets, SORT_BLOCK) + XCD_GROUPS - 1);
-  p.bsum_cap = ceil_div(nscan, SCAN_TILE) + 1;
   const uint64_t mc = m.max_clusters > 0 ? m.max_clusters : 1;
   const uint64_t mt = m.max_tracklets > 0 ? m.max_tracklets : 1;
   p.zblk = L.add<uint32_t>(nur * (p.nblk_s + 1));
@@ -178,7 +174,7 @@ Plan plan_for(const tpc_sizes& m) {
   p.win = L.add<uint32_t>(nur * p.nwin);
   p.cl_list = L.add<uint32_t>(1 + nur * (p.nwin / 4 + 1));  // chunks handed back
   p.crec = L.add<ClusterRec>(m.max_samples > 0 ? m.max_samples : 1);
-  p.bsum = L.add<unsigned long long>(p.bsum_cap);
+  p.bsum = L.add<unsigned long long>(ceil_div(nscan, SCAN_TILE) + 1);  // (tiles and one word)
   p.tot32 = L.add<uint32_t>(1);
   p.chain_len = L.add<uint16_t>(mc / 2 + 1);
   p.chain_me = L.add<uint2>(mc / 2 + 1);
@@ -213,7 +209,6 @@ Plan plan_for(const tpc_sizes& m) {
   p.cm_res = L.add<unsigned long long>(2 * mc);  // two residual codes per hit
   p.cm_tot = L.add<unsigned long long>(2);
   p.cm_info = L.add<uint32_t>(8);
-  p.mg_fs = L.add<uint32_t>(mt);
   p.mg_cell = L.add<uint32_t>(2 * mt);
   p.mg_cnt = L.add<uint32_t>(mg_cells(m));
   p.mg_off = L.add<uint32_t>(mg_cells(m) + 1);
@@ -223,7 +218,6 @@ Plan plan_for(const tpc_sizes& m) {
   p.mg_idx = L.add<uint32_t>(mt);
   p.mg_skey = L.add<uint32_t>(mt);
   p.mg_sidx = L.add<uint32_t>(mt);
-  p.mg_sector = L.add<uint8_t>(mt);
   p.mg_C = L.add<double>(mt);
   p.mg_tgl = L.add<double>(mt);
   p.mg_e = L.add<double>(10 * mt);
@@ -895,7 +889,6 @@ int tpc_create(tpc_ctx** out, const tpc_params* p, const tpc_sizes* max, void* h
   c->cm_res = (uint64_t*)(base + pl.cm_res);
   c->cm_tot = (unsigned long long*)(base + pl.cm_tot);
   c->cm_info = (uint32_t*)(base + pl.cm_info);
-  c->mg_fs = (uint32_t*)(base + pl.mg_fs);
   c->mg_cell = (uint32_t*)(base + pl.mg_cell);
   c->mg_cnt = (uint32_t*)(base + pl.mg_cnt);
   c->mg_off = (uint32_t*)(base + pl.mg_off);
@@ -905,7 +898,6 @@ int tpc_create(tpc_ctx** out, const tpc_params* p, const tpc_sizes* max, void* h
   c->mg_idx = (uint32_t*)(base + pl.mg_idx);
   c->mg_skey = (uint32_t*)(base + pl.mg_skey);
   c->mg_sidx = (uint32_t*)(base + pl.mg_sidx);
-  c->mg_sector = (uint8_t*)(base + pl.mg_sector);
   c->mg_C = (double*)(base + pl.mg_C);
   c->mg_tgl = (double*)(base + pl.mg_tgl);
   c->mg_e = (double*)(base + pl.mg_e);
@@ -915,7 +907,6 @@ int tpc_create(tpc_ctx** out, const tpc_params* p, const tpc_sizes* max, void* h
   c->mg_hxy = (double*)(base + pl.mg_hxy);
   c->d_par = (DevParams*)(base + pl.par);
   c->d_st = (DevStatus*)(base + pl.st);
-  c->bsum_cap = pl.bsum_cap;
   tpc_tuning_default(&c->tune);
   const DevParams dp = make_dev_params(*p);
   DevStatus ds;
@@ -1093,7 +1084,7 @@ int tpc_merge_tracks(tpc_ctx* c, const tpc_clusters* cl, const tpc_tracks* tr, t
       tr->hit_capacity < c->max.max_clusters ? tr->hit_capacity : c->max.max_clusters;
   const uint32_t nzb = mg_nzb(cl->n_time_bins);
   const uint32_t n_cells = ((cl->n_units + 35) / 36) * 2 * MG_NXY * MG_NXY * nzb;
-  const MgSegs S{c->mg_fs, c->mg_sector, c->mg_C, c->mg_tgl, c->mg_e};
+  const MgSegs S{c->mg_C, c->mg_tgl, c->mg_e};
   k_mg_init<<<grid_for((uint64_t)out->capacity * TPC_MERGE_FIT, 256, 4096), 256, 0, s>>>(
       c->mg_cnt, n_cells, out->fit, out->capacity * TPC_MERGE_FIT, c->mg_parent, out->near_tie,
       c->mg_idx, cap, out->n_merged, c->d_st);
