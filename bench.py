@@ -78,17 +78,16 @@ def pmc_traffic(files, stage, kernel_name):
     """HBM bytes per launch of a stage's kernel(s) from the committed rocprofv3
     counter summary (FETCH_SIZE + WRITE_SIZE scaled by a plain copy of known
     size), or None when the kernel sources changed since the counters were
-    taken, the summary is for another launch shape, or none exists."""
+    taken, the summary has no line for the launch shape, or none exists."""
     path = os.path.join(ROOT, "profiles", f"pmc_{stage}_c3_slice.md")
     if not os.path.exists(path):
         return None
-    rec = None
     for line in open(path):
         if line.startswith("traffic_json: "):
             rec = json.loads(line[len("traffic_json: "):])
-    if rec is None or not rec.get("kernel", "").startswith(kernel_name):
-        return None
-    return rec["bytes_per_launch"] if rec.get("source_sha256") == source_hash(files) else None
+            if rec.get("kernel", "").startswith(kernel_name):
+                return rec["bytes_per_launch"] if rec.get("source_sha256") == source_hash(files) else None
+    return None
 
 
 KERNEL_SOURCES = {
