@@ -68,3 +68,37 @@ def test_overlapping_tracklets(tracks, sectors, form):
     for j, t in enumerate(tlt):
         assert np.array_equal(out["hits"][hs[j]:hs[j + 1]], out["follow_hits"][t][won[t]])
     assert (kept >= min_hits).sum() - len(tlt) <= c["n_refit_fail"] + c["n_fallback_fail"]
+
+
+@pytest.mark.parametrize("name", ["sector", "central", "noise"])
+def test_chains_share_no_cluster(name):
+    # what the claims by chains rest on: each word is stored by one tracklet
+    ev = tpcsynth.generate(tpcsynth.config_c2() if name == "central" else
+                           tpcsynth.config_small(100), 79)
+    # (wide windows on noise: most links are wrong, and chains still share nothing)
+    over = dict(win_y=1 << 20, win_z=1 << 20, s_max=1 << 42) if name == "noise" else {}
+    mc, mt = ev.n_samples // 2 + 64, ev.n_samples // 4 + 64
+    reco = tpc.Reco(ev.n_units, ev.n_time_bins, mc, mt, max_samples=ev.n_samples,
+                    param_overrides=over)
+    try:
+        zs = tpc.to_device_zs(ev.pad, ev.time, ev.adc, ev.row_start, ev.n_units, ev.n_time_bins)
+        cl, links = reco.alloc_clusters(ev.n_units, ev.n_time_bins, mc), reco.alloc_links(mc)
+        tl, tr = reco.alloc_tracklets(mt), reco.alloc_tracks(mt, mc, mc, mt)
+        reco.process(zs, cl, links, tl, tr)
+        c = reco.sync()
+        h, hits = tpc.tracklets_to_host(tl), tpc.tracks_to_host(tr, 1, c["n_tracklets"])["follow_hits"]
+        upc = links["upc"].cpu().numpy()
+    finally:
+        reco.close()
+    at, left = h["tl_start"].astype(np.int64), h["tl_len"].astype(np.int64)
+    row = np.searchsorted(cl["crow_start"].cpu().numpy(), at, side="right") - 1
+    seen = np.zeros(c["n_clusters"], np.int64)
+    t = np.arange(len(at))
+    assert len(at) > 20
+    while len(at):
+        np.add.at(seen, at, 1)
+        found = hits[t, row % 152]  # a hit in a row of the chain is the chain's cluster
+        assert ((found < 0) | (found == at)).all()
+        on = left > 1
+        at, left, row, t = upc[at[on]].astype(np.int64), left[on] - 1, row[on] + 1, t[on]
+    assert seen.max() == 1
